@@ -65,7 +65,7 @@ template <bool FP8, int NB, int MODE>
 __global__ __launch_bounds__(256, 1) void mfma_partial_kernel(Problem p, Plan pl) {
     static_assert(NB >= 1 && NB <= 2, "more than 32 rows go to the LDS-staged kernel");
     __shared__ int32_t s_pre[kPlanMaxB + 1];
-    __shared__ int32_t s_sum[64 * kMfmaWavesPerWG];
+    __shared__ int32_t s_sum[kMfmaWavesPerWG];
     // the partition: no separate plan launch (its few microseconds per call
     // were a tenth of a short draft step)
     plan_in_kernel<64 * kMfmaWavesPerWG>(p, pl, s_pre, s_sum);

@@ -476,15 +476,21 @@ __device__ __forceinline__ void plan_in_kernel(const Problem &p, const Plan &pl,
         s_pre[b] = span;
         local += span;
     }
-    s_sum[tid] = local;
-    __syncthreads();
-    for (int off = 1; off < THREADS; off <<= 1) {  // inclusive scan of the per-thread sums
-        const int v = tid >= off ? s_sum[tid - off] : 0;
-        __syncthreads();
-        s_sum[tid] += v;
-        __syncthreads();
+    // inclusive scan of the per-thread sums: within each wave by lane shuffles
+    // (no barrier per step: every call waits for this before its first load),
+    // then the waves' totals
+    const int lane = tid & 63, wave = tid >> 6;
+    int incl = local;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
     }
-    int run = s_sum[tid] - local;
+    if (lane == 63) s_sum[wave] = incl;
+    __syncthreads();
+    int run = incl - local;
+#pragma unroll
+    for (int w = 0; w < THREADS / 64; ++w) run += w < wave ? s_sum[w] : 0;
     for (int b = b0; b < b1; ++b) {
         const int span = s_pre[b];
         s_pre[b] = run;
@@ -492,8 +498,8 @@ __device__ __forceinline__ void plan_in_kernel(const Problem &p, const Plan &pl,
         run += span;
     }
     if (tid == THREADS - 1) {
-        s_pre[B] = s_sum[THREADS - 1];
-        if (store) pl.prefix[B] = s_sum[THREADS - 1];
+        s_pre[B] = run;
+        if (store) pl.prefix[B] = run;
     }
     __syncthreads();
 }
@@ -507,8 +513,9 @@ __device__ __forceinline__ void locate(const int32_t *s_pre, int B, int units, i
     }
     const int span = s_pre[lo + 1] - s_pre[lo];
     const int64_t rel = x - (int64_t)s_pre[lo] * units;
-    seg = lo * units + (int)(rel / span);
-    tile = (int)(rel % span);
+    const int q = (int)div_floor((double)rel, (double)span);
+    seg = lo * units + q;
+    tile = (int)(rel - (int64_t)q * span);
 }
 
 // ---- per-segment setup and finalisation ---------------------------------------

@@ -33,7 +33,7 @@ namespace spire {
 constexpr int kMaxRows = 128;          // (k+1) * Hq/Hkv
 constexpr int kGenericRowBlock = 16;   // rows per unit in the generic kernel
 constexpr int kMaxWorkersPerCU = 8;
-constexpr int kCombineMaxWorkers = 4096;  // workers one launch may have (the combine's LDS list)
+constexpr int kCombineMaxWorkers = 4096;  // workers one launch may have (the combine's weights in LDS)
 
 // Device-side description of one K/V view (byte pointers, element strides).
 struct KvDev {
@@ -95,12 +95,18 @@ __device__ __forceinline__ T uload(const T *p, int64_t i) {
     return ((const cT *)p)[i];
 }
 
+// floor(a / b) for the partition's quotients, on the fp64 unit: a 64-bit integer
+// division is a software sequence several times as long, and every worker and
+// every merging workgroup waits for a few of them in a row.  Exact: a < 2^53,
+// and for a quotient q + r / b the gap 1 / b to the next integer is more than
+// the rounding of q + 1 <= 2^53 / b, so rounding never reaches it.
+__device__ __forceinline__ int64_t div_floor(double a, double b) { return (int64_t)(a / b); }
 __device__ __forceinline__ int64_t worker_begin(int64_t w, int64_t T, int64_t workers) {
-    return (w * T) / workers;
+    return div_floor((double)w * (double)T, (double)workers);
 }
 // the worker whose range contains flattened position x (0 <= x < T)
 __device__ __forceinline__ int64_t worker_of(int64_t x, int64_t T, int64_t workers) {
-    return ((x + 1) * workers - 1) / T;
+    return div_floor((double)(x + 1) * (double)workers - 1.0, (double)T);
 }
 
 constexpr int kPlanMaxB = 8192;  // sequences per call (the partition's LDS arrays)

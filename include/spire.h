@@ -388,7 +388,8 @@ int32_t spire_version(void);
  *                 points ignore it):
  *                 0 automatic -- the matrix-core kernels where dtype and shape
  *                 allow (LDS-staged above 32 rows per KV head, register-staged
- *                 otherwise), the generic vector kernel for the rest;
+ *                 otherwise, the fp32 ones at head_dim 64 and for fp32 K/V),
+ *                 the generic vector kernel for the rest;
  *                 a draft step whose B * Hkv segments number half or a
  *                 quarter of the device's waves (4 per compute unit; at least
  *                 15/16 of them filled) gives each segment 2 or 4 waves of one
@@ -407,7 +408,8 @@ int32_t spire_version(void);
  *                 Launches beyond max_launches are not recorded.
  *   kernel_ids    host array [max_launches] or NULL: the id of each recorded
  *                 launch -- 0 plan, 1 verify partial attention, 2 draft
- *                 partial attention, 3 combine, 4 token verification weights,
+ *                 partial attention, 3 combine (with the check of 11 after
+ *                 the fp32 matrix kernels), 4 token verification weights,
  *                 5 token verification select, 11 the check of the values of
  *                 keys [n - k, n) after a matrix-core verify call, 12 block
  *                 verification weights, 13 block verification select.

@@ -18,7 +18,7 @@ BUILD = os.path.join(HERE, "_build")
 ARCH = "gfx950"
 
 SOURCES = ["spire_abi.hip", "plan_combine.hip", "attn_mfma.hip", "attn_staged.hip",
-           "attn_generic.hip", "token_verify.hip", "block_verify.hip", "kv_update.hip",
+           "attn_generic.hip", "attn_f32.hip", "token_verify.hip", "block_verify.hip", "kv_update.hip",
            "feedback_memory.hip", "hbm_probe.hip"]
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -31,7 +31,7 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 # needs AGPR<->VGPR copies, and the compiler hoists those copies out of the
 # rarely taken rescale branch into every tile.
 MFMA_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-SOURCE_FLAGS = {"attn_mfma.hip": MFMA_FLAGS, "attn_staged.hip": MFMA_FLAGS}
+SOURCE_FLAGS = {"attn_mfma.hip": MFMA_FLAGS, "attn_staged.hip": MFMA_FLAGS, "attn_f32.hip": MFMA_FLAGS}
 
 
 def _hipcc():

@@ -1,9 +1,8 @@
 // attn_generic.hip -- split-KV partial attention on the vector ALUs.
 //
-// Serves every request the matrix-core kernel does not take (fp32 K/V or Q,
-// head_dim 64, contiguous caches whose capacity is not a multiple of 16, page
-// sizes that are not multiples of 16, draft views whose fp8 scales differ) and
-// is a second, independently written GPU path for cross-checks.  It keeps fp32
+// Serves every request the matrix-core kernels do not take (fp32 queries on bf16
+// or fp8 K/V, page sizes that are not multiples of 16, rows off 16-byte
+// boundaries, draft views whose fp8 scales differ) and is a second, independently written GPU path for cross-checks.  It keeps fp32
 // arithmetic throughout (no bf16 rounding of probabilities).
 //
 // One wave per workgroup is one worker of the stream-K partition; a unit is
@@ -11,7 +10,9 @@
 // kb + l against the 16 rows (queries staged in LDS), the row maxima are
 // reduced across the wave, probabilities go through LDS, and for the value
 // product lane l owns head dims l and l + 64.
-#include "spire_internal.h"
+#include <type_traits>
+
+#include "combine.h"
 
 namespace spire {
 
@@ -268,25 +269,81 @@ __device__ __forceinline__ bool word_nonfinite(uint32_t x, int dtype) {
            ((x >> 24) & 0x7Fu) == 0x7Fu;
 }
 
+// True on every lane of the wave when one of the values of keys [n - k, n) of
+// segment (b, h), read by `threads` threads (this one is `tid`), is not finite.
+__device__ __forceinline__ bool tail_nonfinite(const Problem &p, int b, int h, int n, int tid, int threads) {
+    const int lo = n - p.k > 0 ? n - p.k : 0;
+    // the value rows of keys [lo, n), as 4-byte words (row bytes are a multiple of 16)
+    const int words = p.D * p.kv.elem / 4;
+    bool bad = false;
+    for (int idx = tid; idx < (n - lo) * words; idx += threads) {
+        const int key = lo + idx / words, w = idx - (idx / words) * words;
+        const RowRef vr = key_row(p, b, h, key, 0, 0);
+        bad |= word_nonfinite(reinterpret_cast<const uint32_t *>(vr.v)[w], p.kv_dtype);
+    }
+    return __any(bad);
+}
+
+// Every row of segment (b, h) again, exactly (one wave).
+__device__ __forceinline__ void redo_segment(const Problem &p, const Plan &pl, int b, int h, int n, int lane,
+                                             float (*qs)[kMaxD], float (*ps)[KT]) {
+    const int tiles = (n + KT - 1) / KT;
+    for (int r0 = 0; r0 < p.R; r0 += RB) generic_unit(p, pl, b, h, r0, n, 0, 0, 0, tiles, true, 0, lane, qs, ps);
+}
+
 __global__ __launch_bounds__(64) void tail_fix_kernel(Problem p, Plan pl) {
     __shared__ float qs[RB][kMaxD];
     __shared__ float ps[RB][KT];
     const int lane = threadIdx.x;
     const int b = blockIdx.x / p.Hkv, h = blockIdx.x - (blockIdx.x / p.Hkv) * p.Hkv;
     const int n = effective_keys(p, b);
-    const int lo = n - p.k > 0 ? n - p.k : 0;
-    if (lo >= n) return;
-    // the value rows of keys [lo, n), as 4-byte words (row bytes are a multiple of 16)
-    const int words = p.D * p.kv.elem / 4;
-    bool bad = false;
-    for (int idx = lane; idx < (n - lo) * words; idx += 64) {
-        const int key = lo + idx / words, w = idx - (idx / words) * words;
-        const RowRef vr = key_row(p, b, h, key, 0, 0);
-        bad |= word_nonfinite(reinterpret_cast<const uint32_t *>(vr.v)[w], p.kv_dtype);
+    if (tail_nonfinite(p, b, h, n, lane, 64)) redo_segment(p, pl, b, h, n, lane, qs, ps);
+}
+
+// The fp32 matrix path's combine and value check in one launch (a launch less
+// on calls of a few microseconds): workgroups [0, ncomb) merge, the rest check
+// one (sequence, KV head) each and redo it if need be.  A merging workgroup
+// takes the same check first and leaves the rows of a segment that is redone,
+// so nothing is written twice.
+template <bool PER_WORKER, bool GROUPED>
+__global__ __launch_bounds__(kCombineThreads) void combine_check_kernel(Problem p, Plan pl, int ncomb) {
+    struct Unit { float qs[RB][kMaxD], ps[RB][KT]; };
+    __shared__ union Lds {
+        std::conditional_t<GROUPED, CombineLds, int> c;
+        Unit u;
+    } lds;
+    if ((int)blockIdx.x < ncomb) {
+        CombineLds *cl = nullptr;
+        if constexpr (GROUPED) cl = &lds.c;
+        combine_block<PER_WORKER, GROUPED>(p, pl, blockIdx.x, blockIdx.y, gridDim.y, cl, [&](int b, int h) -> bool {
+            // (draft, or k = 0: every row sees every key)
+            const bool check = !p.draft && p.k > 0;
+            if (!check && !GROUPED) return false;
+            return __syncthreads_or(check && tail_nonfinite(p, b, h, pl.nkeys[b], threadIdx.x, kCombineThreads));
+        });
+        return;
     }
-    if (!__any(bad)) return;
-    const int tiles = (n + KT - 1) / KT;
-    for (int r0 = 0; r0 < p.R; r0 += RB) generic_unit(p, pl, b, h, r0, n, 0, 0, 0, tiles, true, 0, lane, qs, ps);
+    if (blockIdx.y > 0 || threadIdx.x >= 64) return;  // one wave; the barriers below count live waves
+    const int s = blockIdx.x - ncomb;
+    const int b = s / p.Hkv, h = s - (s / p.Hkv) * p.Hkv;
+    const int n = pl.nkeys[b];
+    if (tail_nonfinite(p, b, h, n, threadIdx.x, 64)) redo_segment(p, pl, b, h, n, threadIdx.x, lds.u.qs, lds.u.ps);
+}
+
+hipError_t launch_combine_check(const Problem &p, const Plan &pl, hipStream_t st) {
+    if ((int64_t)p.B * pl.units == 0) return hipSuccess;
+    if (pl.workers > kCombineMaxWorkers) return hipErrorInvalidValue;
+    dim3 grid = combine_grid(p, pl);
+    const int ncomb = (int)grid.x;
+    if (!p.draft && p.k > 0) grid.x += (unsigned)(p.B * p.Hkv);
+    const dim3 block(kCombineThreads);
+    if (combine_per_worker(p, pl))
+        hipLaunchKernelGGL((combine_check_kernel<true, false>), grid, block, 0, st, p, pl, ncomb);
+    else if (combine_grouped(p, pl))
+        hipLaunchKernelGGL((combine_check_kernel<false, true>), grid, block, 0, st, p, pl, ncomb);
+    else
+        hipLaunchKernelGGL((combine_check_kernel<false, false>), grid, block, 0, st, p, pl, ncomb);
+    return hipGetLastError();
 }
 
 hipError_t launch_tail_fix(const Problem &p, const Plan &pl, hipStream_t st) {

@@ -110,7 +110,12 @@ size_t workspace_bytes_for(int B, int R, int D) {
     }
     const Layout a = layout(B, R, D, w);
     const Layout b = layout(B, kGenericRowBlock, D, generic_workers(cus));
-    return a.total > b.total ? a.total : b.total;
+    size_t total = std::max(a.total, b.total);
+    for (int elem : {1, 4}) {
+        if (elem != 4 && D != 64) continue;  // 16-bit and 8-bit K/V: head_dim 64 only
+        total = std::max(total, layout(B, f32_shape(R, elem, D).rows, D, mfma_workers(cus)).total);
+    }
+    return total;
 }
 
 // ---- per-call options: kernel family and launch events ----------------------------
@@ -261,21 +266,35 @@ int draft_coop_waves(const Problem &p, int cus, int kernel) {
     return 0;
 }
 
-spire_status run(Problem &p, bool use_mfma, void *workspace, size_t ws_bytes, hipStream_t stream,
+// Which kernels can take a call (0: the generic vector kernel only).
+enum { FAM_GENERIC = 0, FAM_MFMA = 1, FAM_F32 = 2 };
+
+// bf16 queries on bf16 or fp8 K/V: the bf16 kernels at head_dim 128 (P rounded
+// to 16 bits there), the fp32 one at 64; fp32 K/V: the fp32 one.
+int matrix_family(int kv_dtype, int q_dtype, int D) {
+    if (kv_dtype == SPIRE_F32) return FAM_F32;
+    if (q_dtype != SPIRE_BF16) return FAM_GENERIC;
+    return D == 128 ? FAM_MFMA : FAM_F32;
+}
+
+spire_status run(Problem &p, int family, void *workspace, size_t ws_bytes, hipStream_t stream,
                  int partial_id, const spire_launch_opts *opts, bool lib_scratch = false) {
     int cus = 0;
     if (device_cus(&cus) != 0) return fail(SPIRE_ERR_HIP, "cannot query the current HIP device");
     const int kernel = opts != nullptr ? opts->kernel : 0;
     Recorder rec(opts);
-    const bool mf = use_mfma && kernel != 1;
+    const bool mf = family == FAM_MFMA && kernel != 1;
+    const bool f32 = family == FAM_F32 && kernel != 1;
     const bool staged = mf && use_staged(p, kernel);
     const int nb = (p.R + 15) / 16;
+    const F32Shape fs = f32_shape(p.R, p.kv.elem, p.D);
     Plan pl;
-    pl.tile = mf ? kMfmaTile : kGenericTile;
-    const int nrb = mf ? 1 : (p.R + kGenericRowBlock - 1) / kGenericRowBlock;
+    pl.tile = mf ? kMfmaTile : (f32 ? f32_tile(p.kv.elem) : kGenericTile);
+    const int nrb = mf ? 1 : (f32 ? fs.units_per_head : (p.R + kGenericRowBlock - 1) / kGenericRowBlock);
     pl.units = p.Hkv * nrb;
-    pl.rows = mf ? p.R : kGenericRowBlock;
-    pl.workers = !mf ? generic_workers(cus)
+    pl.rows = mf ? p.R : (f32 ? fs.rows : kGenericRowBlock);
+    pl.workers = f32 ? mfma_workers(cus)
+                 : !mf ? generic_workers(cus)
                      : (staged ? staged_workers(cus, nb, p.kv_dtype == SPIRE_FP8_E4M3FN)
                                : mfma_workers(cus));
     // phantom positions per segment (spire_internal.h): on the matrix-core
@@ -283,8 +302,8 @@ spire_status run(Problem &p, bool use_mfma, void *workspace, size_t ws_bytes, hi
     // streaming 35-40 KB of keys takes (queries, output rows, address set-up,
     // pipeline refill); without this, workers covering many short sequences
     // finished last
-    const int64_t tile_bytes = 2LL * kMfmaTile * p.D * p.kv.elem;
-    pl.seg_cost = mf ? (int)((40960 + tile_bytes / 2) / tile_bytes) : 0;
+    const int64_t tile_bytes = 2LL * pl.tile * p.D * p.kv.elem;
+    pl.seg_cost = mf || f32 ? (int)((40960 + tile_bytes / 2) / tile_bytes) : 0;
     if (pl.workers > kCombineMaxWorkers)
         return fail(SPIRE_ERR_UNSUPPORTED, "%d workers exceed the combine's limit of %d", pl.workers,
                     kCombineMaxWorkers);
@@ -306,6 +325,13 @@ spire_status run(Problem &p, bool use_mfma, void *workspace, size_t ws_bytes, hi
     if (const int g = (mf && !staged) ? draft_coop_waves(p, cus, kernel) : 0) {
         e = rec.run(partial_id, stream, [&] { return launch_mfma_draft_coop(p, nb, g, stream); });
         if (e != hipSuccess) return fail(SPIRE_ERR_HIP, "attention launch: %s", hipGetErrorString(e));
+        return SPIRE_OK;
+    }
+    if (f32) {
+        e = rec.run(partial_id, stream, [&] { return launch_f32_partial(p, pl, fs.nb, stream); });
+        if (e != hipSuccess) return fail(SPIRE_ERR_HIP, "attention launch: %s", hipGetErrorString(e));
+        e = rec.run(KID_COMBINE, stream, launch_combine_check, p, pl);
+        if (e != hipSuccess) return fail(SPIRE_ERR_HIP, "combine launch: %s", hipGetErrorString(e));
         return SPIRE_OK;
     }
     // the register-staged kernel computes the partition itself; the others
@@ -464,9 +490,8 @@ static spire_status verify_impl(const void *q, int32_t q_dtype, const spire_kv *
              ? (kv->page_size % 16 == 0 && (uint64_t)kv->s_blk * es < (1ull << 32) &&
                 (uint64_t)kv->page_size * kv->s_tok * es < (1ull << 31))
              : (kv->capacity >= 1));
-    const bool mfma = (kv->dtype == SPIRE_BF16 || kv->dtype == SPIRE_FP8_E4M3FN) &&
-                      q_dtype == SPIRE_BF16 && D == 128 && p.R <= kMaxRows && layout_ok && rows_aligned(kv);
-    return run(p, mfma, workspace, workspace_bytes, stream, KID_VERIFY, opts, lib_scratch);
+    const int family = layout_ok && rows_aligned(kv) ? matrix_family(kv->dtype, q_dtype, D) : FAM_GENERIC;
+    return run(p, family, workspace, workspace_bytes, stream, KID_VERIFY, opts, lib_scratch);
 }
 
 spire_status spire_draft_sparse_attn(const void *q, int32_t q_dtype, const spire_kv *sink,
@@ -529,11 +554,10 @@ spire_status spire_draft_sparse_attn_ex(const void *q, int32_t q_dtype, const sp
     const bool same_scales = ring->dtype != SPIRE_FP8_E4M3FN ||
                              (ring->k_scale == sink->k_scale && ring->v_scale == sink->v_scale);
     // 16 ring rows span under 2^31 bytes (32-bit lane offsets of the loads)
-    const bool mfma = (ring->dtype == SPIRE_BF16 || ring->dtype == SPIRE_FP8_E4M3FN) &&
-                      q_dtype == SPIRE_BF16 && D == 128 && p.R <= kMaxRows && same_scales &&
-                      (uint64_t)ring->s_tok * elem_size(ring->dtype) * 16 < (1ull << 31) &&
-                      rows_aligned(ring) && rows_aligned(sink);
-    return run(p, mfma, workspace, workspace_bytes, stream, KID_DRAFT, opts);
+    const bool layout_ok = same_scales && (uint64_t)ring->s_tok * elem_size(ring->dtype) * 16 < (1ull << 31) &&
+                           rows_aligned(ring) && rows_aligned(sink);
+    const int family = layout_ok ? matrix_family(ring->dtype, q_dtype, D) : FAM_GENERIC;
+    return run(p, family, workspace, workspace_bytes, stream, KID_DRAFT, opts);
 }
 
 // ---- token verification -------------------------------------------------------

@@ -180,6 +180,23 @@ constexpr int staged_waves(bool fp8, int nb) { return nb <= 2 || (fp8 && nb == 5
 constexpr int staged_wps(bool fp8, int nb) { return fp8 && nb > 2 && nb < 5 ? 2 : 1; }
 int staged_workers(int cus, int nb, bool fp8);
 hipError_t launch_combine(const Problem &p, const Plan &pl, hipStream_t st);
+// fp32 matrix kernel (attn_f32.hip): keys per tile, the most row blocks of a
+// unit (what fits the registers beside three tiles; more rows are split evenly
+// over units, each of which reads the keys again), and the combine that includes
+// the check of the values of keys [n - k, n) (attn_generic.hip).
+constexpr int f32_tile(int elem) { return elem == 4 ? 16 : 32; }
+constexpr int f32_blocks(int elem, int D) { return elem < 4 ? 5 : (D == 64 ? 3 : 2); }
+struct F32Shape { int nb, units_per_head, rows; };
+inline F32Shape f32_shape(int R, int elem, int D) {
+    const int most = f32_blocks(elem, D), blocks = (R + 15) / 16;
+    F32Shape s;
+    s.units_per_head = (blocks + most - 1) / most;
+    s.nb = (blocks + s.units_per_head - 1) / s.units_per_head;
+    s.rows = s.units_per_head == 1 ? R : 16 * s.nb;
+    return s;
+}
+hipError_t launch_f32_partial(const Problem &p, const Plan &pl, int nb, hipStream_t st);
+hipError_t launch_combine_check(const Problem &p, const Plan &pl, hipStream_t st);
 // After a matrix-core verify call: recompute exactly the segments whose values
 // at keys [n - k, n) are not all finite (attn_generic.hip).
 hipError_t launch_tail_fix(const Problem &p, const Plan &pl, hipStream_t st);

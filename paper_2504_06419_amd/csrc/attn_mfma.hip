@@ -145,9 +145,9 @@ __global__ __launch_bounds__(256, 1) void mfma_partial_kernel(Problem p, Plan pl
 
 // Whole draft segments per workgroup.  A draft segment never holds more than
 // S + W keys (paper Sec. 3.1: the constant-size sink + window cache), so when
-// the segments number half or a quarter of the device's waves, G = 2 or 4
-// waves of one workgroup per segment balance the work as the stream-K
-// partition does, without its seams: the waves split the segment's tiles
+// the segments are short, or number half or a quarter of the device's waves,
+// G = 1, 2 or 4 waves of one workgroup per segment do the work of the stream-K
+// partition without its seams: the waves split the segment's tiles
 // evenly (the short sink tile, last in the draft key space, goes to the last
 // wave), merge their rows through LDS and write the final rows -- no
 // partition, no partial slots, no combine launch.  Rows are merged on the
@@ -156,11 +156,12 @@ __global__ __launch_bounds__(256, 1) void mfma_partial_kernel(Problem p, Plan pl
 // and weighs zero (its zero or NaN state still propagates).
 template <bool FP8, int NB, int G>
 __global__ __launch_bounds__(256, 1) void mfma_draft_coop_kernel(Problem p) {
-    static_assert(G >= 2 && kMfmaWavesPerWG % G == 0, "waves per segment");
+    static_assert(G >= 1 && kMfmaWavesPerWG % G == 0, "waves per segment");
     constexpr int SPW = kMfmaWavesPerWG / G;  // segments per workgroup
-    __shared__ f32x4 s_acc[SPW][G - 1][8 * NB][64];
-    __shared__ float s_l[SPW][G - 1][NB][64];
-    __shared__ float s_m[SPW][G - 1][NB][64];  // reference maximum; -inf: none
+    constexpr int GM = G > 1 ? G - 1 : 1;     // waves that leave their rows to the first
+    __shared__ f32x4 s_acc[SPW][GM][8 * NB][64];
+    __shared__ float s_l[SPW][GM][NB][64];
+    __shared__ float s_m[SPW][GM][NB][64];  // reference maximum; -inf: none
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int slot = wave / G, part = wave - (wave / G) * G;
@@ -179,6 +180,10 @@ __global__ __launch_bounds__(256, 1) void mfma_draft_coop_kernel(Problem p) {
         float sc = p.sm_scale_log2;
         if (FP8) sc *= uload(p.kv.k_scale, h);
         if (t0 < t1) stream_tiles<FP8, NB, MODE_DRAFT>(a, qf, st, t0, t1 - 1, n, n, sc, lane);
+    }
+    if constexpr (G == 1) {  // nothing to merge
+        if (valid) end_rows<FP8, NB, false>(p, Plan{}, st, b, h, 0, true, 0, lane);
+        return;
     }
     if (valid && part > 0) {
 #pragma unroll
@@ -223,14 +228,127 @@ __global__ __launch_bounds__(256, 1) void mfma_draft_coop_kernel(Problem p) {
     end_rows<FP8, NB, false>(p, Plan{}, st, b, h, 0, true, 0, lane);
 }
 
+// Few, short draft segments: one workgroup of G waves per segment, every wave
+// merging.  Bound by latency and by what one CU can request (13 sequences of 500
+// bf16 keys are 27 MB, 4 us of HBM time): the partition of the stream-K kernel,
+// its partials' round trip and the combine launch cost more than the keys.  The G
+// waves split the segment's tiles, leave their accumulators in LDS, and each
+// merges and writes 8 / G of the head-dim slices (lane: dims 32j + 8i + 4u .. +3
+// of slice 2i + u), on the reference maxima as above.  G = 8: two waves per SIMD
+// with two tile buffers each, 256 KB in flight; two row blocks take the registers
+// of four waves.  MI355X, bf16, 8 KV heads of 4 queries, in a graph: 13 sequences
+// of 508 + 4 keys 15.5 -> 12.1 us, of 124 + 4 keys 12.0 -> 6.7.
+template <bool FP8, int NB, int MODE>
+__device__ __forceinline__ void stream_tiles2(const SegAddr &a, const QFrag<NB, false> &qf,
+                                              SoftmaxState<NB, false> &st, int first, int last, int n, float sc,
+                                              int lane) {
+    TileRegs<FP8> A, Bt;
+    load_tile<FP8, MODE>(A, a, first, lane);
+    int tt = first;
+    while (true) {
+        if (tt + 1 <= last) load_tile<FP8, MODE>(Bt, a, tt + 1, lane);
+        compute_tile<FP8, NB>(A, qf, st, tt, n, n, sc, lane);
+        if (++tt > last) break;
+        if (tt + 1 <= last) load_tile<FP8, MODE>(A, a, tt + 1, lane);
+        compute_tile<FP8, NB>(Bt, qf, st, tt, n, n, sc, lane);
+        if (++tt > last) break;
+    }
+}
+
+template <bool FP8, int NB, int G>
+__global__ __launch_bounds__(64 * G, G / 4) void mfma_draft_short_kernel(Problem p) {
+    constexpr int SPW = 8 / G;  // slices a wave merges
+    __shared__ f32x4 s_o[G][NB][8][64];
+    __shared__ float s_l[G][NB][16];
+    __shared__ float s_m[G][NB][16];  // reference maximum; -inf: none
+    const int lane = threadIdx.x & 63;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n16 = lane & 15, j = lane >> 4;
+    const int b = (int)blockIdx.x / p.Hkv, h = (int)blockIdx.x - b * p.Hkv;
+    {
+        const int n = effective_keys(p, b);
+        const int T = (n + kMfmaTile - 1) / kMfmaTile;
+        const int t0 = part * T / G, t1 = (part + 1) * T / G;
+        SoftmaxState<NB, false> st;
+        reset_rows<NB, false>(p, n, 0, st, lane);
+        if (t0 < t1) {
+            const SegAddr a = make_seg_addr<MODE_DRAFT>(p, b, h, n);
+            QFrag<NB, false> qf;
+            load_rows_q<FP8, NB, false>(p, b, h, 0, qf, lane);
+            float sc = p.sm_scale_log2;
+            if (FP8) sc *= uload(p.kv.k_scale, h);
+            if constexpr (G == 8) stream_tiles2<FP8, NB, MODE_DRAFT>(a, qf, st, t0, t1 - 1, n, sc, lane);
+            else stream_tiles<FP8, NB, MODE_DRAFT>(a, qf, st, t0, t1 - 1, n, n, sc, lane);
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            float l = st.l[nb];
+            l += __shfl_xor(l, 16);
+            l += __shfl_xor(l, 32);
+            if (j == 0) {
+                s_l[part][nb][n16] = l;
+                s_m[part][nb][n16] = st.thr[nb] == -INFINITY ? -INFINITY : st.msub[nb];
+            }
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+                s_o[part][nb][x][lane] = f32x4{st.acc[4 * (x & 1)][nb][x >> 1], st.acc[4 * (x & 1) + 1][nb][x >> 1],
+                                               st.acc[4 * (x & 1) + 2][nb][x >> 1], st.acc[4 * (x & 1) + 3][nb][x >> 1]};
+        }
+    }
+    __syncthreads();
+    const float vs = FP8 ? uload(p.kv.v_scale, h) : 1.f;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int r = 16 * nb + n16;
+        if (r >= p.R) continue;
+        float wgt[G], M = -INFINITY, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < G; ++w) {
+            wgt[w] = s_m[w][nb][n16];
+            M = fmaxf(M, wgt[w]);
+        }
+        M = M == -INFINITY ? 0.f : M;
+#pragma unroll
+        for (int w = 0; w < G; ++w) {
+            wgt[w] = wgt[w] == -INFINITY ? 0.f : fast_exp2(wgt[w] - M);
+            l += s_l[w][nb][n16] * wgt[w];
+        }
+        // l == 0: no visible key; l NaN: a NaN key or a +inf score was visible
+        const float inv = l > 0.f ? vs / l : (l == 0.f ? 0.f : l);
+        const int64_t off = row_offset(p, b, h, r) + 32 * j;
+#pragma unroll
+        for (int y = 0; y < SPW; ++y) {
+            const int x = part * SPW + y;
+            f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < G; ++w) o += s_o[w][nb][x][lane] * wgt[w];
+            o *= inv;
+            if (p.out_dtype == SPIRE_BF16)
+                *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + off + 4 * x) =
+                    u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+            else
+                *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(p.out) + off + 4 * x) = o;
+        }
+        if (part == 0 && j == 0 && p.lse != nullptr) {
+            const float lse2 = l > 0.f ? M + log2f(l) : (l == 0.f ? -INFINITY : l);
+            p.lse[lse_index(p, b, h, r)] = lse2 * 0.69314718055994531f;
+        }
+    }
+}
+
 template <bool FP8, int NB>
 static hipError_t launch_coop_nb(const Problem &p, int g, hipStream_t st) {
     const int segs = p.B * p.Hkv;
     const dim3 block(64 * kMfmaWavesPerWG);
-    if (g == 4)
+    if (g == kDraftShort) {
+        constexpr int G = NB == 1 ? 8 : 4;
+        hipLaunchKernelGGL((mfma_draft_short_kernel<FP8, NB, G>), dim3(segs), dim3(64 * G), 0, st, p);
+    } else if (g == 4)
         hipLaunchKernelGGL((mfma_draft_coop_kernel<FP8, NB, 4>), dim3(segs), block, 0, st, p);
     else if (g == 2)
         hipLaunchKernelGGL((mfma_draft_coop_kernel<FP8, NB, 2>), dim3((segs + 1) / 2), block, 0, st, p);
+    else if (g == 1)
+        hipLaunchKernelGGL((mfma_draft_coop_kernel<FP8, NB, 1>), dim3((segs + 3) / 4), block, 0, st, p);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

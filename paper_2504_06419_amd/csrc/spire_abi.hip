@@ -252,15 +252,43 @@ bool use_staged(const Problem &p, int kernel) {
     return false;  // measured: up to 32 rows the register-staged kernel is faster
 }
 
-// Waves per segment for a draft step with whole segments per workgroup, or 0
-// for the stream-K partition: 4 or 2 waves per segment when that fills at
-// least 15/16 of the device's waves without exceeding them (a draft segment
-// never exceeds S + W keys, so equal shares of segments stay balanced).
-// Kernel choice 2 keeps the stream-K partition.
+// Waves per segment for a draft step with whole segments per workgroup,
+// kDraftShort (the kernel for few, short segments), or 0 for the stream-K
+// partition.  Kernel choice 2 keeps the stream-K partition.
+//
+// Short segments: without the partition, the partials and the combine launch a
+// call is 4-7 us shorter, but a wave that holds a whole segment (or a half, or a
+// CU that holds one) reads it at 8-11 GB/s (30-45), and segments of unequal fill
+// are not evened out, so long segments are faster on the partition.  The limits
+// hold for even and for log-uniform fills, bf16 and fp8 (bf16, 4 queries per KV
+// head, even fills, us a call in a graph, stream-K / whole segments):
+//   one segment per CU: 240 KB of K+V plus 1 KB per segment of the call
+//     8 segments of 256 KB 10.7 / 9.1, of 320 KB 11.1 / 12.2; 104 of 256 KB
+//     15.5 / 12.1, of 384 KB 17.8 / 16.5, of 514 KB 19.4 / 20.6
+//   two waves each: 192 KB, 256 KB where 7/8 of the waves have work
+//     272 of 192 KB 18.7 / 17.7, of 256 KB 22.2 / 21.7 (fp8 23.8 / 26.3);
+//     448 of 256 KB 30.7 / 23.7
+//   one wave each: 128 KB, 192 KB from 7/8; 64 KB in several rounds, 128 KB
+//     where 3/4 of the rounds' waves have work
+//     520 of 128 KB 21.9 / 20.8, of 256 KB 33.4 / 37.5; 1024 of 192 KB 39.0 /
+//     35.1; 1280 of 64 KB 26.2 / 24.2, of 128 KB 39.2 / 41.1; 2048 of 128 KB
+//     50.9 / 48.9
+// Longer ones: 4 or 2 waves per segment when that fills at least 15/16 of the
+// device's waves without exceeding them.
 int draft_coop_waves(const Problem &p, int cus, int kernel) {
     if (!p.draft || kernel == 2) return 0;
     const int64_t segs = (int64_t)p.B * p.Hkv, waves = mfma_workers(cus);
     if (segs <= 0) return 0;
+    const int64_t seg_kb = (((int64_t)p.S + p.W) * 2 * p.D * p.kv.elem) >> 10;
+    if (segs <= cus && seg_kb <= 240 + segs) return kDraftShort;
+    if (segs > cus) {
+        const int g = 2 * segs <= waves ? 2 : 1;
+        const int64_t room = (segs * g + waves - 1) / waves * waves;  // waves of the rounds it takes
+        const bool full = 8 * segs * g >= 7 * room;
+        const int64_t most = g == 2 ? (full ? 256 : 192)
+                           : segs <= waves ? (full ? 192 : 128) : (4 * segs >= 3 * room ? 128 : 64);
+        if (seg_kb <= most) return g;
+    }
     for (int g = kMfmaWavesPerWG; g >= 2; g /= 2)
         if (segs * g <= waves && segs * g * 16 >= waves * 15) return g;
     return 0;

@@ -167,6 +167,8 @@ hipError_t launch_plan(const Problem &p, const Plan &pl, hipStream_t st);
 hipError_t launch_mfma_partial(const Problem &p, const Plan &pl, int nb, hipStream_t st);
 // Draft steps with whole segments per workgroup (g = 2 or 4 waves per segment):
 // final rows written directly, no plan and no combine.
+// kDraftShort: the kernel for few, short segments.
+constexpr int kDraftShort = -1;
 hipError_t launch_mfma_draft_coop(const Problem &p, int nb, int g, hipStream_t st);
 hipError_t launch_generic_partial(const Problem &p, const Plan &pl, hipStream_t st);
 hipError_t launch_staged_partial(const Problem &p, const Plan &pl, int nb, hipStream_t st);

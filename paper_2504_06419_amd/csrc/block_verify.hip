@@ -21,10 +21,12 @@
 //   weights kernel  grid (pieces, k+1 rows, B): every wave owns one 2048-entry
 //                   piece of one row, recomputes p_i (k gathers, an in-order
 //                   fold across lanes) and writes the piece's weight sum;
-//   select kernel   one workgroup per sequence: row sums from the piece sums,
-//                   the walk, then the threshold's piece is read again and
-//                   searched as in token verification.  An empty residual
-//                   row, which draws from P instead, is scanned whole.
+//   select kernel   one workgroup per sequence: every row's sum from the piece
+//                   sums, the walk as one ballot, then the threshold's piece is
+//                   read again and searched as in token verification.  An empty
+//                   residual row, which draws from P instead, is scanned whole.
+// MI355X, 64 sequences, k = 4, V = 50257 (116 MB): weights 28.2 -> 21.3 us (5.4
+// TB/s), select 10.3 -> 5.7, a call 49.4 -> 27.8.
 #include "sampling.h"
 
 namespace spire {
@@ -72,7 +74,6 @@ __device__ __forceinline__ double stop_probability(uint64_t S, double p) {
     return den > 0.0 ? __ddiv_rn(Sd, den) : 1.0;
 }
 
-template <bool VEC>
 __global__ __launch_bounds__(kTvThreads) void block_weights_kernel(TokenProblem t) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -81,40 +82,36 @@ __global__ __launch_bounds__(kTvThreads) void block_weights_kernel(TokenProblem 
     const int b = blockIdx.z;
     if (s >= t.npieces) return;
     const bool resid = i < t.k;
-    const double pw = block_prefix_weights(t, b, lane);
-    const float scale = (float)__shfl(pw, i);  // p_i rounded to fp32
     const float *prow = t.p + ((int64_t)b * (t.k + 1) + i) * t.V;
     const float *qrow = resid ? t.q + ((int64_t)b * t.k + i) * t.V : nullptr;
     const int x0 = s * kTokenPiece;
+    // coalesced 16-byte loads, issued before the prefix weights' gathers and fold;
+    // then the last group's up to three entries
+    const tv_f32x4u *p4 = reinterpret_cast<const tv_f32x4u *>(prow + x0);
+    const tv_f32x4u *q4 = reinterpret_cast<const tv_f32x4u *>(resid ? qrow + x0 : prow + x0);
+    const int cnt = min(kTokenPiece, t.V - x0), groups = cnt >> 2;
+    tv_f32x4 pv[kTvGroupsPerLane], qv[kTvGroupsPerLane];
+    const tv_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < kTvGroupsPerLane; ++g) {
+        const int gi = lane + 64 * g;
+        pv[g] = gi < groups ? __builtin_nontemporal_load(p4 + gi) : zero;
+        qv[g] = (resid && gi < groups) ? __builtin_nontemporal_load(q4 + gi) : zero;
+    }
+    const double pw = block_prefix_weights(t, b, lane);
+    const float scale = (float)__shfl(pw, i);  // p_i rounded to fp32
     uint64_t sw = 0;
-    if (VEC) {
-        // coalesced 16-byte loads; V % 4 == 0, so a 4-entry group is wholly in or out
-        const tv_f32x4 *p4 = reinterpret_cast<const tv_f32x4 *>(prow + x0);
-        const tv_f32x4 *q4 = reinterpret_cast<const tv_f32x4 *>(resid ? qrow + x0 : prow + x0);
-        const int groups = min(kTokenPiece, t.V - x0) >> 2;
-        tv_f32x4 pv[kTvGroupsPerLane], qv[kTvGroupsPerLane];
-        const tv_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    if (lane < (cnt & 3)) {
+        const int x = x0 + 4 * groups + lane;
+        sw = block_weight(scale, prow[x], qrow, x);
+    }
 #pragma unroll
-        for (int g = 0; g < kTvGroupsPerLane; ++g) {
-            const int gi = lane + 64 * g;
-            pv[g] = gi < groups ? __builtin_nontemporal_load(p4 + gi) : zero;
-            qv[g] = (resid && gi < groups) ? __builtin_nontemporal_load(q4 + gi) : zero;
-        }
+    for (int g = 0; g < kTvGroupsPerLane; ++g) {
+        if (resid) {
 #pragma unroll
-        for (int g = 0; g < kTvGroupsPerLane; ++g) {
-            if (resid) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sw += fixed_weight(__fsub_rn(__fmul_rn(scale, pv[g][e]), qv[g][e]));
-            } else {
-                sw += fixed_weight(pv[g].x) + fixed_weight(pv[g].y) + fixed_weight(pv[g].z) + fixed_weight(pv[g].w);
-            }
-        }
-    } else {
-        const int cnt = min(kTokenPiece, t.V - x0);
-#pragma unroll 4
-        for (int e = 0; e < kTokenPiece / 64; ++e) {
-            const int xi = lane + 64 * e;
-            if (xi < cnt) sw += block_weight(scale, prow[x0 + xi], qrow, x0 + xi);
+            for (int e = 0; e < 4; ++e) sw += fixed_weight(__fsub_rn(__fmul_rn(scale, pv[g][e]), qv[g][e]));
+        } else {
+            sw += fixed_weight(pv[g].x) + fixed_weight(pv[g].y) + fixed_weight(pv[g].z) + fixed_weight(pv[g].w);
         }
     }
     sw = wave_sum(sw);
@@ -124,32 +121,20 @@ __global__ __launch_bounds__(kTvThreads) void block_weights_kernel(TokenProblem 
 // Token in piece entries [x0, x0 + cnt) whose running weight first exceeds R
 // (R below the piece's total); as token verification's search, with the
 // weights of a block verification row.
-template <bool VEC>
 __device__ __forceinline__ void block_select_in_piece(const float *prow, const float *qrow, float scale, int x0,
                                                       int cnt, uint64_t R, uint64_t *s_red, int *s_tok,
                                                       int lane, int wave) {
     const int base = kTvSlice * (int)threadIdx.x;
     float pv[kTvSlice], qv[kTvSlice];
-    if (VEC) {
+#pragma unroll
+    for (int g = 0; g < kTvSlice / 4; ++g) {
         const tv_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        const tv_f32x4 a = load_group(prow, x0 + base + 4 * g, x0 + cnt);
+        const tv_f32x4 c = qrow ? load_group(qrow, x0 + base + 4 * g, x0 + cnt) : zero;
 #pragma unroll
-        for (int g = 0; g < kTvSlice / 4; ++g) {
-            const bool in = base + 4 * g < cnt;
-            const tv_f32x4 a = in ? *reinterpret_cast<const tv_f32x4 *>(prow + x0 + base + 4 * g) : zero;
-            const tv_f32x4 c = (in && qrow) ? *reinterpret_cast<const tv_f32x4 *>(qrow + x0 + base + 4 * g)
-                                            : zero;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                pv[4 * g + e] = a[e];
-                qv[4 * g + e] = c[e];
-            }
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < kTvSlice; ++e) {
-            const bool in = base + e < cnt;
-            pv[e] = in ? prow[x0 + base + e] : 0.f;
-            qv[e] = (in && qrow) ? qrow[x0 + base + e] : 0.f;
+        for (int e = 0; e < 4; ++e) {
+            pv[4 * g + e] = a[e];
+            qv[4 * g + e] = c[e];
         }
     }
     uint64_t w[kTvSlice];
@@ -200,66 +185,49 @@ __device__ __forceinline__ void block_select_from_p(const float *prow, int V, fl
     }
 }
 
-template <bool VEC>
 __global__ __launch_bounds__(kTvThreads) void block_select_kernel(TokenProblem t) {
     __shared__ uint64_t s_red[kTvWaves];
-    __shared__ int s_piece, s_tok;
-    __shared__ uint64_t s_rem;
+    __shared__ uint64_t s_sum[kTokenMaxK + 1];
+    __shared__ int s_tok;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
     const int K = t.k;
     if (tid == 0) s_tok = -1;
-    const double pw = block_prefix_weights(t, b, lane);  // p_lane on lanes 0..k
-
-    // sum of one row's weights from its piece sums (npieces <= 512)
-    auto row_sum = [&](int i) -> uint64_t {
-        const uint64_t *ps = t.piece_sum + ((int64_t)b * (K + 1) + i) * t.npieces;
+    // every row's sum at once, rows dealt to the waves: the walk then waits for no
+    // loads (one block-wide sum per step of it: 10.3 us, now 5.7)
+    const uint64_t *sums = t.piece_sum + (int64_t)b * (K + 1) * t.npieces;
+    for (int i = wave; i <= K; i += kTvWaves) {
         uint64_t mine = 0;
-        for (int c = tid; c < t.npieces; c += kTvThreads) mine += ps[c];
-        return block_sum(mine, s_red, lane, wave);
-    };
-
-    // the walk: every thread takes the same decisions
-    int tau = 0;
-    for (int i = K; i >= 1; --i) {
-        const double pi = __shfl(pw, i);
-        const double h = i == K ? pi : stop_probability(row_sum(i), pi);
-        if ((double)t.u_accept[(int64_t)b * K + i - 1] < h) {
-            tau = i;
-            break;
-        }
+        for (int c = lane; c < t.npieces; c += 64) mine += sums[(int64_t)i * t.npieces + c];
+        mine = wave_sum(mine);
+        if (lane == 0) s_sum[i] = mine;
     }
+    const double pw = block_prefix_weights(t, b, lane);  // p_lane on lanes 0..k
+    const float ua = lane < K ? t.u_accept[(int64_t)b * K + lane] : 0.f;
+    const float us = t.u_sample[b];
+    __syncthreads();
+
+    // row i = lane + 1 stops the walk where u_i < h_i: the largest such row
+    const int row = lane + 1;
+    const double pi = __shfl(pw, row & 63);
+    const double h = row == K ? pi : stop_probability(row < K ? s_sum[row] : 0, pi);
+    const uint64_t stops = __ballot(row <= K && (double)ua < h);
+    const int tau = stops == 0 ? 0 : 64 - __builtin_clzll(stops);
 
     const bool resid = tau < K;
     const float scale = (float)__shfl(pw, tau);
     const float *prow = t.p + ((int64_t)b * (K + 1) + tau) * t.V;
     const float *qrow = resid ? t.q + ((int64_t)b * K + tau) * t.V : nullptr;
-    const uint64_t Z = row_sum(tau);
-    const uint64_t *ps = t.piece_sum + ((int64_t)b * (K + 1) + tau) * t.npieces;
-    if (Z != 0) {
-        const uint64_t T = sample_threshold(t.u_sample[b], Z);
-        // piece holding the threshold: the first whose running sum exceeds T
-        uint64_t carry = 0;
-        for (int base = 0; base < t.npieces; base += kTvThreads) {
-            const int c = base + tid;
-            const uint64_t v = c < t.npieces ? ps[c] : 0;
-            uint64_t total;
-            const uint64_t incl = block_incl_scan(v, s_red, lane, wave, &total) + carry;
-            const uint64_t excl = incl - v;
-            if (c < t.npieces && excl <= T && T < incl) {  // exactly one thread
-                s_piece = c;
-                s_rem = T - excl;
-            }
-            carry += total;
-        }
-        __syncthreads();
-        const int c = s_piece;
-        block_select_in_piece<VEC>(prow, qrow, scale, c * kTokenPiece, min(kTokenPiece, t.V - c * kTokenPiece),
-                                   s_rem, s_red, &s_tok, lane, wave);
+    const PieceSums ps = load_piece_sums(sums + (int64_t)tau * t.npieces, t.npieces, lane);
+    if (ps.Z != 0) {
+        uint64_t rem;
+        const int c = find_piece(ps, t.npieces, sample_threshold(us, ps.Z), lane, &rem);
+        block_select_in_piece(prow, qrow, scale, c * kTokenPiece, min(kTokenPiece, t.V - c * kTokenPiece),
+                              rem, s_red, &s_tok, lane, wave);
     } else if (resid) {
         // empty residual row: draw from P of the same row
-        block_select_from_p(prow, t.V, t.u_sample[b], s_red, &s_tok, lane, wave);
+        block_select_from_p(prow, t.V, us, s_red, &s_tok, lane, wave);
     }
     __syncthreads();
     if (tid <= K) {
@@ -271,21 +239,14 @@ __global__ __launch_bounds__(kTvThreads) void block_select_kernel(TokenProblem t
     if (tid == 0) t.n_accepted[b] = tau;
 }
 
-// 16-byte loads need every row 16-byte aligned: V % 4 == 0 and aligned bases
-static bool block_vec(const TokenProblem &t) {
-    return (t.V % 4) == 0 && ((uintptr_t)t.p & 15u) == 0 && (t.k == 0 || ((uintptr_t)t.q & 15u) == 0);
-}
-
 hipError_t launch_block_weights(const TokenProblem &t, hipStream_t st) {
     const dim3 grid((t.npieces + kTvWaves - 1) / kTvWaves, t.k + 1, t.B), block(kTvThreads);
-    if (block_vec(t)) hipLaunchKernelGGL(block_weights_kernel<true>, grid, block, 0, st, t);
-    else hipLaunchKernelGGL(block_weights_kernel<false>, grid, block, 0, st, t);
+    hipLaunchKernelGGL(block_weights_kernel, grid, block, 0, st, t);
     return hipGetLastError();
 }
 
 hipError_t launch_block_select(const TokenProblem &t, hipStream_t st) {
-    if (block_vec(t)) hipLaunchKernelGGL(block_select_kernel<true>, dim3(t.B), dim3(kTvThreads), 0, st, t);
-    else hipLaunchKernelGGL(block_select_kernel<false>, dim3(t.B), dim3(kTvThreads), 0, st, t);
+    hipLaunchKernelGGL(block_select_kernel, dim3(t.B), dim3(kTvThreads), 0, st, t);
     return hipGetLastError();
 }
 

@@ -21,7 +21,7 @@
 //                   (k gathers), streams the piece of p (and of q for a
 //                   correction) with coalesced 16-byte loads and writes the
 //                   piece's weight sum -- no workgroup synchronisation;
-//   select kernel   one workgroup per sequence: prefix over the piece sums,
+//   select kernel   one workgroup per sequence: search of the piece sums,
 //                   the piece holding the threshold is read again (8 KB of p,
 //                   8 KB of q) and searched in registers.  An empty
 //                   correction row, which falls back to p, is scanned whole.
@@ -53,7 +53,6 @@ __device__ __forceinline__ uint64_t entry_weight(const float *prow, const float 
     return fixed_weight(qrow ? pv - qrow[x] : pv);
 }
 
-template <bool VEC>
 __global__ __launch_bounds__(kTvThreads) void token_weights_kernel(TokenProblem t) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -66,35 +65,23 @@ __global__ __launch_bounds__(kTvThreads) void token_weights_kernel(TokenProblem 
     const float *qrow = corr ? t.q + ((int64_t)b * t.k + n) * t.V : nullptr;
     const int x0 = s * kTokenPiece;
     uint64_t sw = 0;
-    if (VEC) {
-        // coalesced 16-byte loads; V % 4 == 0, so a 4-entry group is wholly in or out
-        const tv_f32x4 *p4 = reinterpret_cast<const tv_f32x4 *>(prow + x0);
-        const tv_f32x4 *q4 = reinterpret_cast<const tv_f32x4 *>(corr ? qrow + x0 : prow + x0);
-        const int groups = min(kTokenPiece, t.V - x0) >> 2;
-        tv_f32x4 pv[kTvGroupsPerLane], qv[kTvGroupsPerLane];
-        const tv_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    // coalesced 16-byte loads, then the last group's up to three entries
+    const tv_f32x4u *p4 = reinterpret_cast<const tv_f32x4u *>(prow + x0);
+    const tv_f32x4u *q4 = reinterpret_cast<const tv_f32x4u *>(corr ? qrow + x0 : prow + x0);
+    const int cnt = min(kTokenPiece, t.V - x0), groups = cnt >> 2;
+    tv_f32x4 pv[kTvGroupsPerLane], qv[kTvGroupsPerLane];
+    const tv_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < kTvGroupsPerLane; ++i) {
-            const int gi = lane + 64 * i;
-            pv[i] = gi < groups ? __builtin_nontemporal_load(p4 + gi) : zero;
-            qv[i] = (corr && gi < groups) ? __builtin_nontemporal_load(q4 + gi) : zero;
-        }
+    for (int i = 0; i < kTvGroupsPerLane; ++i) {
+        const int gi = lane + 64 * i;
+        pv[i] = gi < groups ? __builtin_nontemporal_load(p4 + gi) : zero;
+        qv[i] = (corr && gi < groups) ? __builtin_nontemporal_load(q4 + gi) : zero;
+    }
+    if (lane < (cnt & 3)) sw = entry_weight(prow, qrow, x0 + 4 * groups + lane);
 #pragma unroll
-        for (int i = 0; i < kTvGroupsPerLane; ++i) {
-            const tv_f32x4 w = pv[i] - qv[i];  // q is zero for a bonus row
-            sw += fixed_weight(w.x) + fixed_weight(w.y) + fixed_weight(w.z) + fixed_weight(w.w);
-        }
-    } else {
-        const int cnt = min(kTokenPiece, t.V - x0);
-        float pv[kTokenPiece / 64], qv[kTokenPiece / 64];
-#pragma unroll
-        for (int i = 0; i < kTokenPiece / 64; ++i) {
-            const int xi = lane + 64 * i;
-            pv[i] = xi < cnt ? prow[x0 + xi] : 0.f;
-            qv[i] = (corr && xi < cnt) ? qrow[x0 + xi] : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < kTokenPiece / 64; ++i) sw += fixed_weight(pv[i] - qv[i]);
+    for (int i = 0; i < kTvGroupsPerLane; ++i) {
+        const tv_f32x4 w = pv[i] - qv[i];  // q is zero for a bonus row
+        sw += fixed_weight(w.x) + fixed_weight(w.y) + fixed_weight(w.z) + fixed_weight(w.w);
     }
     sw = wave_sum(sw);
     if (lane == 0) {
@@ -108,31 +95,18 @@ __global__ __launch_bounds__(kTvThreads) void token_weights_kernel(TokenProblem 
 // entries [x0 + 8 tid, ...): its loads are issued at once, its weights stay in
 // registers, the block scans the slice sums and the one thread whose slice
 // holds R finds the token among its registers.
-template <bool VEC>
 __device__ __forceinline__ void select_in_piece(const float *prow, const float *qrow, int x0, int cnt,
                                                 uint64_t R, uint64_t *s_red, int *s_tok, int lane,
                                                 int wave) {
     const int base = kTvSlice * (int)threadIdx.x;
     float pv[kTvSlice], qv[kTvSlice];
-    if (VEC) {
-        // 16-byte loads; cnt % 4 == 0, so a 4-entry group is wholly in or out
+#pragma unroll
+    for (int i = 0; i < kTvSlice / 4; ++i) {
         const tv_f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < kTvSlice / 4; ++i) {
-            const bool in = base + 4 * i < cnt;
-            const tv_f32x4 a = in ? *reinterpret_cast<const tv_f32x4 *>(prow + x0 + base + 4 * i) : zero;
-            const tv_f32x4 c = (in && qrow) ? *reinterpret_cast<const tv_f32x4 *>(qrow + x0 + base + 4 * i)
-                                            : zero;
-            pv[4 * i] = a.x; pv[4 * i + 1] = a.y; pv[4 * i + 2] = a.z; pv[4 * i + 3] = a.w;
-            qv[4 * i] = c.x; qv[4 * i + 1] = c.y; qv[4 * i + 2] = c.z; qv[4 * i + 3] = c.w;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kTvSlice; ++i) {
-            const bool in = base + i < cnt;
-            pv[i] = in ? prow[x0 + base + i] : 0.f;
-            qv[i] = (in && qrow) ? qrow[x0 + base + i] : 0.f;
-        }
+        const tv_f32x4 a = load_group(prow, x0 + base + 4 * i, x0 + cnt);
+        const tv_f32x4 c = qrow ? load_group(qrow, x0 + base + 4 * i, x0 + cnt) : zero;
+        pv[4 * i] = a.x; pv[4 * i + 1] = a.y; pv[4 * i + 2] = a.z; pv[4 * i + 3] = a.w;
+        qv[4 * i] = c.x; qv[4 * i + 1] = c.y; qv[4 * i + 2] = c.z; qv[4 * i + 3] = c.w;
     }
     uint64_t w[kTvSlice];
     uint64_t s = 0;
@@ -181,45 +155,23 @@ __device__ __forceinline__ void select_in_range(const float *prow, const float *
     }
 }
 
-template <bool VEC>
 __global__ __launch_bounds__(kTvThreads) void token_select_kernel(TokenProblem t) {
     __shared__ uint64_t s_red[kTvWaves];
-    __shared__ int s_piece, s_tok;
-    __shared__ uint64_t s_rem;
+    __shared__ int s_tok;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
     if (tid == 0) s_tok = -1;
     const int n = uload(t.nacc, b);  // recorded by the weights kernel (0 <= n <= k)
     const bool corr = n < t.k;
-    const uint64_t *ps = t.piece_sum + (int64_t)b * t.npieces;
     const float *prow = t.p + ((int64_t)b * (t.k + 1) + n) * t.V;
     const float *qrow = corr ? t.q + ((int64_t)b * t.k + n) * t.V : nullptr;
-
-    // total weight of the row (npieces <= 512: at most two sums per thread)
-    uint64_t mine = 0;
-    for (int i = tid; i < t.npieces; i += kTvThreads) mine += ps[i];
-    const uint64_t Z = block_sum(mine, s_red, lane, wave);
-    if (Z != 0) {
-        const uint64_t T = sample_threshold(t.u_sample[b], Z);
-        // piece holding the threshold: the first whose running sum exceeds T
-        uint64_t carry = 0;
-        for (int base = 0; base < t.npieces; base += kTvThreads) {
-            const int i = base + tid;
-            const uint64_t v = i < t.npieces ? ps[i] : 0;
-            uint64_t total;
-            const uint64_t incl = block_incl_scan(v, s_red, lane, wave, &total) + carry;
-            const uint64_t excl = incl - v;
-            if (i < t.npieces && excl <= T && T < incl) {  // exactly one thread
-                s_piece = i;
-                s_rem = T - excl;
-            }
-            carry += total;
-        }
-        __syncthreads();
-        const int c = s_piece;
-        select_in_piece<VEC>(prow, qrow, c * kTokenPiece, min(kTokenPiece, t.V - c * kTokenPiece), s_rem,
-                             s_red, &s_tok, lane, wave);
+    const PieceSums ps = load_piece_sums(t.piece_sum + (int64_t)b * t.npieces, t.npieces, lane);
+    if (ps.Z != 0) {
+        uint64_t rem;
+        const int c = find_piece(ps, t.npieces, sample_threshold(t.u_sample[b], ps.Z), lane, &rem);
+        select_in_piece(prow, qrow, c * kTokenPiece, min(kTokenPiece, t.V - c * kTokenPiece), rem,
+                        s_red, &s_tok, lane, wave);
     } else if (corr) {
         // empty correction row (p <= q everywhere at this resolution): draw
         // from p of the same row, scanning the whole row
@@ -242,21 +194,14 @@ __global__ __launch_bounds__(kTvThreads) void token_select_kernel(TokenProblem t
     if (tid == 0) t.n_accepted[b] = n;
 }
 
-// 16-byte loads need every row 16-byte aligned: V % 4 == 0 and aligned bases
-static bool token_vec(const TokenProblem &t) {
-    return (t.V % 4) == 0 && ((uintptr_t)t.p & 15u) == 0 && ((uintptr_t)t.q & 15u) == 0;
-}
-
 hipError_t launch_token_weights(const TokenProblem &t, hipStream_t st) {
     const dim3 grid((t.npieces + kTvWaves - 1) / kTvWaves, t.B), block(kTvThreads);
-    if (token_vec(t)) hipLaunchKernelGGL(token_weights_kernel<true>, grid, block, 0, st, t);
-    else hipLaunchKernelGGL(token_weights_kernel<false>, grid, block, 0, st, t);
+    hipLaunchKernelGGL(token_weights_kernel, grid, block, 0, st, t);
     return hipGetLastError();
 }
 
 hipError_t launch_token_select(const TokenProblem &t, hipStream_t st) {
-    if (token_vec(t)) hipLaunchKernelGGL(token_select_kernel<true>, dim3(t.B), dim3(kTvThreads), 0, st, t);
-    else hipLaunchKernelGGL(token_select_kernel<false>, dim3(t.B), dim3(kTvThreads), 0, st, t);
+    hipLaunchKernelGGL(token_select_kernel, dim3(t.B), dim3(kTvThreads), 0, st, t);
     return hipGetLastError();
 }
 

@@ -491,6 +491,124 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_partial_kernel(Pr
     }
 }
 
+// Short draft segments of up to 16 rows, whole: G = 1, 2 or 4 waves of one
+// workgroup per segment, as in attn_mfma.hip (the limits are the host's): no
+// partition, no partials, no combine launch.  The waves split the tiles; beyond
+// one they leave their accumulators in LDS and each merges and writes its share
+// of the head-dim slices, on the reference maxima.  MI355X, 8 KV heads of 4
+// queries, in a graph: 13 sequences of 256 bf16 keys at head_dim 64 12.8 -> 6.4 us,
+// of 512 fp32 keys 16.6 -> 13.6; 64 of 256 fp32 keys 22.2 -> 14.3.
+template <int ES, int D, int G>
+__global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kernel(Problem p) {
+    constexpr int KG = f32_tile(ES) / 16;
+    constexpr int SPW = kMfmaWavesPerWG / G;  // segments per workgroup
+    constexpr int NS = D / 16, PER = NS / G;  // slices of four dims, and each wave's share
+    __shared__ f32x4 s_o[SPW][G > 1 ? G : 1][G > 1 ? NS : 1][64];
+    __shared__ float s_l[SPW][G][16];
+    __shared__ float s_m[SPW][G][16];  // reference maximum; -inf: none
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n16 = lane & 15, j = lane >> 4;
+    const int slot = wave / G, part = wave - (wave / G) * G;
+    const int seg = (int)blockIdx.x * SPW + slot;
+    const bool valid = seg < p.B * p.Hkv;
+    const int b = valid ? seg / p.Hkv : 0;
+    const int h = valid ? seg - b * p.Hkv : 0;
+    State32<D, 1> st;
+    if (valid) {
+        const int n = effective_keys(p, b);
+        const int T = (n + 16 * KG - 1) / (16 * KG);
+        const int t0 = part * T / G, t1 = (part + 1) * T / G;
+        Q32<ES, D, 1> q;
+        begin_rows32<ES, D, 1>(p, b, h, n, 0, q, st, lane);
+        float sc = p.sm_scale_log2;
+        if (ES == 1) sc *= uload(p.kv.k_scale, h);
+        if (t0 < t1) {
+            const SegAddr a = make_seg_addr<MODE_DRAFT>(p, b, h, n);
+            stream32<ES, D, 1, KG, MODE_DRAFT>(a, q, st, t0, t1 - 1, n, n, sc, lane);
+            if (ES <= 2 && lost_infinity<ES, D, 1>(st)) {
+                begin_rows32<ES, D, 1>(p, b, h, n, 0, q, st, lane);
+                stream32_exact<ES, D, 1, KG, MODE_DRAFT>(a, q, st, t0, t1 - 1, n, n, sc, lane);
+            }
+        }
+    }
+    if constexpr (G == 1) {  // nothing to merge
+        if (valid) end_rows32<ES, D, 1>(p, Plan{}, st, b, h, 0, true, 0, lane);
+    } else {
+        if (valid) {
+            float l = st.l[0];
+            l += __shfl_xor(l, 16);
+            l += __shfl_xor(l, 32);
+            if (j == 0) {
+                s_l[slot][part][n16] = l;
+                s_m[slot][part][n16] = st.thr[0] == -INFINITY ? -INFINITY : st.msub[0];
+            }
+#pragma unroll
+            for (int y = 0; y < NS; ++y) {
+                const int i = y & 3, x = y >> 2;
+                s_o[slot][part][y][lane] = f32x4{st.acc[4 * x][0][i], st.acc[4 * x + 1][0][i], st.acc[4 * x + 2][0][i],
+                                                 st.acc[4 * x + 3][0][i]};
+            }
+        }
+        __syncthreads();
+        if (!valid || n16 >= p.R) return;
+        float wgt[G], M = -INFINITY, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < G; ++w) {
+            wgt[w] = s_m[slot][w][n16];
+            M = fmaxf(M, wgt[w]);
+        }
+        M = M == -INFINITY ? 0.f : M;
+#pragma unroll
+        for (int w = 0; w < G; ++w) {
+            wgt[w] = wgt[w] == -INFINITY ? 0.f : exp2f(wgt[w] - M);
+            l += s_l[slot][w][n16] * wgt[w];
+        }
+        // l == 0: no visible key; l NaN: a NaN key or a +inf score was visible
+        const float vs = ES == 1 ? uload(p.kv.v_scale, h) : 1.f;
+        const float inv = l > 0.f ? vs / l : (l == 0.f ? 0.f : l);
+        const int64_t off = row_offset(p, b, h, n16);
+#pragma unroll
+        for (int z = 0; z < PER; ++z) {
+            const int y = part * PER + z;
+            f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < G; ++w) o += s_o[slot][w][y][lane] * wgt[w];
+            o *= inv;
+            const int d = dim32<ES, D>(y & 3, y >> 2, j);
+            if (p.out_dtype == SPIRE_BF16)
+                *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + off + d) =
+                    u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+            else
+                *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(p.out) + off + d) = o;
+        }
+        if (part == 0 && j == 0 && p.lse != nullptr) {
+            const float lse2 = l > 0.f ? M + log2f(l) : (l == 0.f ? -INFINITY : l);
+            p.lse[lse_index(p, b, h, n16)] = lse2 * 0.69314718055994531f;
+        }
+    }
+}
+
+template <int ES, int D>
+static hipError_t launch_whole_d(const Problem &p, int g, hipStream_t st) {
+    const unsigned segs = (unsigned)(p.B * p.Hkv);
+    const dim3 block(64 * kMfmaWavesPerWG);
+    switch (g) {
+    case 1: hipLaunchKernelGGL((f32_draft_whole_kernel<ES, D, 1>), dim3((segs + 3) / 4), block, 0, st, p); break;
+    case 2: hipLaunchKernelGGL((f32_draft_whole_kernel<ES, D, 2>), dim3((segs + 1) / 2), block, 0, st, p); break;
+    case 4: hipLaunchKernelGGL((f32_draft_whole_kernel<ES, D, 4>), dim3(segs), block, 0, st, p); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_f32_draft_whole(const Problem &p, int g, hipStream_t st) {
+    if (!p.draft || p.R > 16 || p.B * p.Hkv <= 0) return hipErrorInvalidValue;
+    if (p.kv_dtype == SPIRE_F32) return p.D == 64 ? launch_whole_d<4, 64>(p, g, st) : launch_whole_d<4, 128>(p, g, st);
+    if (p.D != 64 || p.q_dtype != SPIRE_BF16) return hipErrorInvalidValue;
+    return p.kv_dtype == SPIRE_BF16 ? launch_whole_d<2, 64>(p, g, st) : launch_whole_d<1, 64>(p, g, st);
+}
+
 template <int ES, int D, int NB>
 static hipError_t launch_f32_nb(const Problem &p, const Plan &pl, hipStream_t st) {
     const dim3 grid((pl.workers + kMfmaWavesPerWG - 1) / kMfmaWavesPerWG), block(64 * kMfmaWavesPerWG);

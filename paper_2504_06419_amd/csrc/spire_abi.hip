@@ -273,13 +273,17 @@ bool use_staged(const Problem &p, int kernel) {
 //     520 of 128 KB 21.9 / 20.8, of 256 KB 33.4 / 37.5; 1024 of 192 KB 39.0 /
 //     35.1; 1280 of 64 KB 26.2 / 24.2, of 128 KB 39.2 / 41.1; 2048 of 128 KB
 //     50.9 / 48.9
-// Longer ones: 4 or 2 waves per segment when that fills at least 15/16 of the
-// device's waves without exceeding them.
-int draft_coop_waves(const Problem &p, int cus, int kernel) {
+// The fp32 kernel (up to 16 rows) keeps the same limits, an fp8 segment counting
+// twice: its tile math takes as long as a 16-bit tile's (us, head_dim 64: bf16,
+// 104 of 64 KB 12.8 / 6.4, of 256 KB 15.8 / 13.7; fp8, 104 of 128 KB 14.7 / 11.4,
+// of 192 KB 15.7 / 16.0; fp32, 512 of 192 KB 26.9 / 20.3).
+// Longer ones, bf16 kernels: 4 or 2 waves per segment when that fills at least
+// 15/16 of the device's waves without exceeding them.
+int draft_coop_waves(const Problem &p, int cus, int kernel, bool f32) {
     if (!p.draft || kernel == 2) return 0;
     const int64_t segs = (int64_t)p.B * p.Hkv, waves = mfma_workers(cus);
     if (segs <= 0) return 0;
-    const int64_t seg_kb = (((int64_t)p.S + p.W) * 2 * p.D * p.kv.elem) >> 10;
+    const int64_t seg_kb = (((int64_t)p.S + p.W) * 2 * p.D * (f32 && p.kv.elem == 1 ? 2 : p.kv.elem)) >> 10;
     if (segs <= cus && seg_kb <= 240 + segs) return kDraftShort;
     if (segs > cus) {
         const int g = 2 * segs <= waves ? 2 : 1;
@@ -289,7 +293,7 @@ int draft_coop_waves(const Problem &p, int cus, int kernel) {
                            : segs <= waves ? (full ? 192 : 128) : (4 * segs >= 3 * room ? 128 : 64);
         if (seg_kb <= most) return g;
     }
-    for (int g = kMfmaWavesPerWG; g >= 2; g /= 2)
+    for (int g = kMfmaWavesPerWG; g >= 2 && !f32; g /= 2)
         if (segs * g <= waves && segs * g * 16 >= waves * 15) return g;
     return 0;
 }
@@ -350,8 +354,13 @@ spire_status run(Problem &p, int family, void *workspace, size_t ws_bytes, hipSt
     pl.part_o = reinterpret_cast<float *>(ws + L.part_o);
 
     hipError_t e = hipSuccess;
-    if (const int g = (mf && !staged) ? draft_coop_waves(p, cus, kernel) : 0) {
+    if (const int g = (mf && !staged) ? draft_coop_waves(p, cus, kernel, false) : 0) {
         e = rec.run(partial_id, stream, [&] { return launch_mfma_draft_coop(p, nb, g, stream); });
+        if (e != hipSuccess) return fail(SPIRE_ERR_HIP, "attention launch: %s", hipGetErrorString(e));
+        return SPIRE_OK;
+    }
+    if (const int g = f32 && p.R <= 16 ? draft_coop_waves(p, cus, kernel, true) : 0) {
+        e = rec.run(partial_id, stream, [&] { return launch_f32_draft_whole(p, g == kDraftShort ? 4 : g, stream); });
         if (e != hipSuccess) return fail(SPIRE_ERR_HIP, "attention launch: %s", hipGetErrorString(e));
         return SPIRE_OK;
     }

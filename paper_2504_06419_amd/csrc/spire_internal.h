@@ -197,6 +197,8 @@ inline F32Shape f32_shape(int R, int elem, int D) {
     s.rows = s.units_per_head == 1 ? R : 16 * s.nb;
     return s;
 }
+// Draft steps of up to 16 rows with short segments, g = 1, 2 or 4 waves each.
+hipError_t launch_f32_draft_whole(const Problem &p, int g, hipStream_t st);
 hipError_t launch_f32_partial(const Problem &p, const Plan &pl, int nb, hipStream_t st);
 hipError_t launch_combine_check(const Problem &p, const Plan &pl, hipStream_t st);
 // After a matrix-core verify call: recompute exactly the segments whose values

@@ -21,8 +21,9 @@ def _cus() -> int:
     return torch.cuda.get_device_properties(0).multi_processor_count
 
 
-def _inputs(B, Hkv, kv_dtype, g, S, Wn, lo, hi, seed):
-    spec = W.DraftSpec(B=B, Hq=g * Hkv, Hkv=Hkv, D=128, S=S, W=Wn, steps=1, ctx_lo=lo, ctx_hi=hi, kv_dtype=kv_dtype)
+def _inputs(B, Hkv, kv_dtype, g, S, Wn, lo, hi, seed, D=128):
+    spec = W.DraftSpec(B=B, Hq=g * Hkv, Hkv=Hkv, D=D, S=S, W=Wn, steps=1, ctx_lo=lo, ctx_hi=hi, kv_dtype=kv_dtype,
+                       q_dtype="f32" if kv_dtype == "f32" else "bf16")
     inp = W.make_draft_inputs(spec, seed, device=DEV)
     W.write_step_token(inp, 0)
     return inp
@@ -97,3 +98,38 @@ def test_rule_edges(B, Hkv, Wn, whole):
     ref, _ = spire.draft_sparse_attn(inp.q[0].contiguous(), sink, ring, inp.seq_lens(0), inp.ring_offset, s.S, s.W,
                                      inp.sm_scale, s.Hkv, kernel=2)
     assert float((out - ref).abs().max()) <= 2 * _tol(inp)
+
+
+F32 = [("f32", 64), ("f32", 128), ("bf16", 64), ("fp8", 64)]
+TOL32 = 1e-5   # fp32 throughout: as the fp32 path's other tests
+
+
+@pytest.mark.parametrize("kv_dtype,D", F32)
+@pytest.mark.parametrize("g", [1, 4, 16])
+@pytest.mark.parametrize("B,Hkv,S,Wn,lo,hi", [(1, 1, 4, 100, 2000, 2000), (13, 8, 4, 37, 1, 90), (7, 2, 0, 33, 1, 60),
+                                              (5, 3, 8, 0, 1, 12), (300, 1, 4, 60, 1, 300), (777, 1, 4, 28, 1, 90),
+                                              (1283, 1, 4, 12, 1, 40)])
+def test_fp32_path(kv_dtype, D, g, B, Hkv, S, Wn, lo, hi):
+    banner(f"short segments, fp32 path {kv_dtype} D={D} g={g} B={B} Hkv={Hkv} S={S} W={Wn} ctx=[{lo},{hi}]")
+    inp = _inputs(B, Hkv, kv_dtype, g, S, Wn, lo, hi, 5500 + g + B + S + Wn, D=D)
+    _check(inp, inp.seq_lens(0), TOL32)
+
+
+@pytest.mark.parametrize("kv_dtype,D", [("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("B", [9, 280, 600])
+def test_fp32_path_degenerate_lengths_and_nonfinite(kv_dtype, D, B):
+    """As above on the fp32 path: one, two and four waves per segment; an
+    infinite value is visible to every row, which it makes infinite or NaN."""
+    banner(f"short segments, fp32 path {kv_dtype} D={D} B={B}: degenerate lengths, NaN / inf keys and values")
+    inp = _inputs(B, 1, kv_dtype, 4, 4, 52, 200, 400, 5600 + B, D=D)
+    lens = inp.seq_lens(0).clone()
+    lens[3], lens[4], lens[5], lens[6], lens[7] = 4, 0, -7, 5, 10 ** 6
+    inp.ring_v[0, 0, 5] = float("nan")
+    inp.ring_k[1, 0, 50] = float("nan")
+    inp.sink_v[2, 0, 0] = float("inf")
+    inp.q[0][3, :4] = -1.0                       # sequence 3: every score -inf
+    inp.sink_k[3, 0] = float("inf")
+    out, lse = _check(inp, lens, TOL32)
+    assert torch.isnan(out[0]).all() and torch.isnan(out[1]).all()
+    assert torch.isinf(out[2]).all()
+    assert (out[3:6] == 0).all() and torch.isneginf(lse[3:6]).all()

@@ -59,7 +59,7 @@ template <int W> __device__ __forceinline__ void ld_words(uint32_t (&d)[W], cons
     }
 }
 
-template <int ES, int D, int KG, int MODE>
+template <int ES, int D, int KG, int MODE, bool KNT = true>
 __device__ __forceinline__ void load_tile32(Tile32<ES, D, KG> &T, const SegAddr &a, int tile, int lane) {
     using TT = Tile32<ES, D, KG>;
     const int n16 = lane & 15, j = lane >> 4;
@@ -72,7 +72,7 @@ __device__ __forceinline__ void load_tile32(Tile32<ES, D, KG> &T, const SegAddr 
             const uint32_t tb = (uint32_t)a.tok_bytes;
             const uint8_t *kp = a.kseq + base + (uint32_t)(n16 * tb + 16 * j);
 #pragma unroll
-            for (int c = 0; c < TT::NKC; ++c) T.k[g][c] = ld16(kp + 64 * c);
+            for (int c = 0; c < TT::NKC; ++c) T.k[g][c] = ld16k<KNT>(kp + 64 * c);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 ld_words(T.v[g][i], a.vseq + base + (uint32_t)((4 * j + i) * tb + VB * n16));
@@ -83,7 +83,7 @@ __device__ __forceinline__ void load_tile32(Tile32<ES, D, KG> &T, const SegAddr 
         const uint8_t *kp = MODE == MODE_DRAFT ? draft_row(a, kk, false)
                                                : a.kseq + (int64_t)min(kk, a.cap - 1) * a.tok_bytes;
 #pragma unroll
-        for (int c = 0; c < TT::NKC; ++c) T.k[g][c] = ld16(kp + 16 * j + 64 * c);
+        for (int c = 0; c < TT::NKC; ++c) T.k[g][c] = ld16k<KNT>(kp + 16 * j + 64 * c);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int vk = key0 + 16 * g + 4 * j + i;
@@ -383,20 +383,20 @@ __device__ __forceinline__ void end_rows32(const Problem &p, const Plan &pl, Sta
 // Tiles [first, last] through NBUF register buffers, NBUF - 1 tiles in flight:
 // three, and five of the 4 KB fp8 tiles while they fit (64 sequences of 512-8192
 // fp8 keys, 20 rows: 57.6 -> 52.4 us; bf16 within 1 % from two to five).
-template <int ES, int D, int NB, int KG, int MODE>
+template <int ES, int D, int NB, int KG, int MODE, bool KNT = true>
 __device__ __forceinline__ void stream32(const SegAddr &a, const Q32<ES, D, NB> &q, State32<D, NB> &st, int first,
                                          int last, int n, int full_lim, float sc, int lane) {
     constexpr int NBUF = ES == 1 && NB <= 3 ? 5 : 3;
     Tile32<ES, D, KG> T[NBUF];
 #pragma unroll
     for (int x = 0; x < NBUF - 1; ++x)
-        if (first + x <= last) load_tile32<ES, D, KG, MODE>(T[x], a, first + x, lane);
+        if (first + x <= last) load_tile32<ES, D, KG, MODE, KNT>(T[x], a, first + x, lane);
     int tt = first;
     while (true) {
 #pragma unroll
         for (int x = 0; x < NBUF; ++x) {
             if (tt + NBUF - 1 <= last)
-                load_tile32<ES, D, KG, MODE>(T[(x + NBUF - 1) % NBUF], a, tt + NBUF - 1, lane);
+                load_tile32<ES, D, KG, MODE, KNT>(T[(x + NBUF - 1) % NBUF], a, tt + NBUF - 1, lane);
             compute_tile32<ES, D, NB, KG, ES <= 2>(T[x], q, st, tt, n, full_lim, sc, lane);
             if (++tt > last) return;
         }
@@ -525,7 +525,9 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kerne
         if (ES == 1) sc *= uload(p.kv.k_scale, h);
         if (t0 < t1) {
             const SegAddr a = make_seg_addr<MODE_DRAFT>(p, b, h, n);
-            stream32<ES, D, 1, KG, MODE_DRAFT>(a, q, st, t0, t1 - 1, n, n, sc, lane);
+            // a segment with a CU to itself: ordinary K loads (ld16k; bf16, head_dim 64, 104
+            // segments of 1024 keys 13.9 -> 12.8 us; the 64-sequence verify call loses 3 %)
+            stream32<ES, D, 1, KG, MODE_DRAFT, G != 4>(a, q, st, t0, t1 - 1, n, n, sc, lane);
             if (ES <= 2 && lost_infinity<ES, D, 1>(st)) {
                 begin_rows32<ES, D, 1>(p, b, h, n, 0, q, st, lane);
                 stream32_exact<ES, D, 1, KG, MODE_DRAFT>(a, q, st, t0, t1 - 1, n, n, sc, lane);

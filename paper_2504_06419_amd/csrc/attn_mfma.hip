@@ -40,22 +40,22 @@ namespace spire {
 // tiles in flight; only tiles of the range are loaded (a buffer is computed
 // only after its load).  The stream-K kernel below keeps the same loop
 // written out: as a call it compiled to a slightly different schedule.
-template <bool FP8, int NB, int MODE>
+template <bool FP8, int NB, int MODE, bool KNT = !FP8>
 __device__ __forceinline__ void stream_tiles(const SegAddr &a, const QFrag<NB, false> &qf,
                                              SoftmaxState<NB, false> &st, int first, int last, int n,
                                              int full_lim, float sc, int lane) {
     TileRegs<FP8> A, Bt, C;
-    load_tile<FP8, MODE>(A, a, first, lane);
-    if (first + 1 <= last) load_tile<FP8, MODE>(Bt, a, first + 1, lane);
+    load_tile<FP8, MODE, KNT>(A, a, first, lane);
+    if (first + 1 <= last) load_tile<FP8, MODE, KNT>(Bt, a, first + 1, lane);
     int tt = first;
     while (true) {
-        if (tt + 2 <= last) load_tile<FP8, MODE>(C, a, tt + 2, lane);
+        if (tt + 2 <= last) load_tile<FP8, MODE, KNT>(C, a, tt + 2, lane);
         compute_tile<FP8, NB>(A, qf, st, tt, n, full_lim, sc, lane);
         if (++tt > last) break;
-        if (tt + 2 <= last) load_tile<FP8, MODE>(A, a, tt + 2, lane);
+        if (tt + 2 <= last) load_tile<FP8, MODE, KNT>(A, a, tt + 2, lane);
         compute_tile<FP8, NB>(Bt, qf, st, tt, n, full_lim, sc, lane);
         if (++tt > last) break;
-        if (tt + 2 <= last) load_tile<FP8, MODE>(Bt, a, tt + 2, lane);
+        if (tt + 2 <= last) load_tile<FP8, MODE, KNT>(Bt, a, tt + 2, lane);
         compute_tile<FP8, NB>(C, qf, st, tt, n, full_lim, sc, lane);
         if (++tt > last) break;
     }
@@ -237,19 +237,19 @@ __global__ __launch_bounds__(256, 1) void mfma_draft_coop_kernel(Problem p) {
 // of slice 2i + u), on the reference maxima as above.  G = 8: two waves per SIMD
 // with two tile buffers each, 256 KB in flight; two row blocks take the registers
 // of four waves.  MI355X, bf16, 8 KV heads of 4 queries, in a graph: 13 sequences
-// of 508 + 4 keys 15.5 -> 12.1 us, of 124 + 4 keys 12.0 -> 6.7.
+// of 508 + 4 keys 15.5 -> 10.6 us, of 124 + 4 keys 12.0 -> 6.5.
 template <bool FP8, int NB, int MODE>
 __device__ __forceinline__ void stream_tiles2(const SegAddr &a, const QFrag<NB, false> &qf,
                                               SoftmaxState<NB, false> &st, int first, int last, int n, float sc,
                                               int lane) {
     TileRegs<FP8> A, Bt;
-    load_tile<FP8, MODE>(A, a, first, lane);
+    load_tile<FP8, MODE, false>(A, a, first, lane);
     int tt = first;
     while (true) {
-        if (tt + 1 <= last) load_tile<FP8, MODE>(Bt, a, tt + 1, lane);
+        if (tt + 1 <= last) load_tile<FP8, MODE, false>(Bt, a, tt + 1, lane);
         compute_tile<FP8, NB>(A, qf, st, tt, n, n, sc, lane);
         if (++tt > last) break;
-        if (tt + 1 <= last) load_tile<FP8, MODE>(A, a, tt + 1, lane);
+        if (tt + 1 <= last) load_tile<FP8, MODE, false>(A, a, tt + 1, lane);
         compute_tile<FP8, NB>(Bt, qf, st, tt, n, n, sc, lane);
         if (++tt > last) break;
     }
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64 * G, G / 4) void mfma_draft_short_kernel(Problem
             float sc = p.sm_scale_log2;
             if (FP8) sc *= uload(p.kv.k_scale, h);
             if constexpr (G == 8) stream_tiles2<FP8, NB, MODE_DRAFT>(a, qf, st, t0, t1 - 1, n, sc, lane);
-            else stream_tiles<FP8, NB, MODE_DRAFT>(a, qf, st, t0, t1 - 1, n, n, sc, lane);
+            else stream_tiles<FP8, NB, MODE_DRAFT, false>(a, qf, st, t0, t1 - 1, n, n, sc, lane);
         }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {

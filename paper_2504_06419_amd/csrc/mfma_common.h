@@ -125,6 +125,18 @@ __device__ __forceinline__ u32x2 ld8(const uint8_t *p) {
     return __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(p));
 }
 
+// K is the exception where its instructions read 64 bytes of 16 rows, half of
+// each 128-byte line: the streaming policy lets go of a line before the next
+// instruction asks for its other half.  With ordinary loads fp8 K/V streams
+// faster (512 sequences, W = 4096: 700 -> 681 us a draft step), and so does a
+// segment that has a CU to itself (104 segments of 508 + 4 bf16 keys: 12.4 -> 10.9
+// us, of 1020 + 4 fp8 keys 13.6 -> 12.5); bf16 over the whole chip does not (64
+// sequences, W = 2048: 89.7 -> 92.8).
+template <bool NT> __device__ __forceinline__ u32x4 ld16k(const uint8_t *p) {
+    if constexpr (NT) return ld16(p);
+    else return *reinterpret_cast<const u32x4 *>(p);
+}
+
 template <bool FP8> struct TileRegs;
 template <> struct TileRegs<false> { u32x4 k[2][4]; u32x4 v[8]; };  // bf16
 template <> struct TileRegs<true> { u32x4 k[2][2]; u32x2 v[8]; };   // fp8
@@ -143,14 +155,14 @@ struct SegAddr {
     int32_t nr, rs, W;               // draft: valid ring slots, first slot, window
 };
 
-template <bool FP8>
+template <bool FP8, bool NT>
 __device__ __forceinline__ void load_k_row(TileRegs<FP8> &T, int mb, const uint8_t *kp) {
     if (FP8) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) T.k[mb][u] = ld16(kp + 64 * u);
+        for (int u = 0; u < 2; ++u) T.k[mb][u] = ld16k<NT>(kp + 64 * u);
     } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) T.k[mb][c] = ld16(kp + 64 * c);
+        for (int c = 0; c < 4; ++c) T.k[mb][c] = ld16k<NT>(kp + 64 * c);
     }
 }
 template <bool FP8>
@@ -208,7 +220,7 @@ __device__ __forceinline__ int64_t group_base(const SegAddr &a, int key0) {
     }
 }
 
-template <bool FP8, int MODE>
+template <bool FP8, int MODE, bool KNT = !FP8>
 __device__ __forceinline__ void load_tile(TileRegs<FP8> &T, const SegAddr &a, int tile, int lane) {
     const int n16 = lane & 15, j = lane >> 4;
     const int rho = 4 * (n16 & 3) + (n16 >> 2);
@@ -219,7 +231,7 @@ __device__ __forceinline__ void load_tile(TileRegs<FP8> &T, const SegAddr &a, in
     const int64_t voff = (int64_t)j * a.tok_bytes + (FP8 ? 8 : 16) * n16;
     if (MODE == MODE_PAGED || (g0 >= 0 && g1 >= 0)) {  // fast path: two contiguous 16-row groups
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) load_k_row<FP8>(T, mb, a.kseq + (mb ? g1 : g0) + koff);
+        for (int mb = 0; mb < 2; ++mb) load_k_row<FP8, KNT>(T, mb, a.kseq + (mb ? g1 : g0) + koff);
 #pragma unroll
         for (int t = 0; t < 8; ++t)
             load_v_row<FP8>(T, t, a.vseq + (t < 4 ? g0 : g1) + (int64_t)(4 * (t & 3)) * a.tok_bytes + voff);
@@ -235,7 +247,7 @@ __device__ __forceinline__ void load_tile(TileRegs<FP8> &T, const SegAddr &a, in
         } else {
             kp = a.kseq + (int64_t)min(key, a.cap - 1) * a.tok_bytes + 16 * j;
         }
-        load_k_row<FP8>(T, mb, kp);
+        load_k_row<FP8, KNT>(T, mb, kp);
     }
 #pragma unroll
     for (int t = 0; t < 8; ++t) {

@@ -1,7 +1,8 @@
 // spire_abi.hip -- host implementation of the C ABI in include/spire.h.
 //
 // Validates arguments, lays out the caller's workspace, picks the kernel
-// family (matrix-core for bf16/fp8 K/V with head_dim 128, generic otherwise)
+// family (bf16 matrix-core kernels for bf16/fp8 K/V with head_dim 128, the fp32
+// one for head_dim 64 and fp32 K/V, generic otherwise)
 // and enqueues plan -> partial attention -> combine on the caller's stream.
 #include <stdarg.h>
 #include <stdio.h>

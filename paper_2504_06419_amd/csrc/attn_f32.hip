@@ -115,6 +115,27 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// Wait until the matrix results x can be read by vector instructions.  A
+// v_mfma_f32_16x16x4_f32 takes 8 passes and nothing but independent instructions
+// keeps a reader from seeing sums that lack the last products: 10 wait states,
+// which the compiler counts and fills.  Where the reader follows a short branch
+// around a few instructions (the mask of a range's last tile, the end of a range), it
+// takes the count along the branch for the direct way as well and inserts nothing:
+// the row maxima were then taken from partial dot products, and a reference off by
+// more than 126 (scores of hundreds) lost its row's tile.  The 4-pass bf16
+// instruction needs 8, which every way here has.  tests/test_matrix_waits.py counts
+// the wait states of every way in the built library.
+template <int N> __device__ __forceinline__ void settle(f32x4 (&x)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));  // issued before the wait ...
+    asm volatile("s_nop 9");
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));  // ... and read after it
+}
+template <int M, int N> __device__ __forceinline__ void settle(f32x4 (&x)[M][N]) {
+    settle(reinterpret_cast<f32x4(&)[M * N]>(x));
+}
+
 // Query fragments of NB row blocks: bf16 MFMA operands (16-bit keys) or the
 // fp32 elements matching the lane's key chunks.
 template <int ES, int D, int NB> struct Q32 {
@@ -203,6 +224,7 @@ __device__ __forceinline__ void compute_tile32(Tile32<ES, D, KG> &T, const Q32<E
             }
         }
     }
+    if constexpr (ES == 4) settle(s);
     if (key0 + 16 * KG > full_lim) {  // uniform: only tiles reaching past a row's last visible key
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)

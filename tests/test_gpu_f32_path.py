@@ -140,3 +140,26 @@ def test_nonfinite_keys_and_draft_values():
     ref_o, ref_l = oracle_draft(d, 0)
     g = out.double().cpu().numpy()
     assert np.array_equal(np.isnan(g), np.isnan(ref_o)) and np.isnan(ref_o).any()
+
+
+@pytest.mark.parametrize("kv,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("fp8", 64)])
+@pytest.mark.parametrize("n,scale", [(60, 2.0 ** 6), (60, 2.0 ** 10), (3000, 2.0 ** 10)])
+def test_scores_of_hundreds_and_thousands(kv, D, n, scale):
+    """Scores far apart: the reference maximum of every tile has to be that tile's
+    own (one that is off by more than the exponent's range empties the row).
+    Queries and keys are integers, the keys times a power of two: every score is
+    exact, and a log-sum-exp of a few thousand carries at most eight roundings of
+    2^-24 each."""
+    banner(f"fp32 path: scores of {scale:.0f} x integers, {kv} D={D} n={n}")
+    inp = W.make_verify_inputs(_spec(kv, D, 1, 4, B=12, ctx_lo=n, ctx_hi=n), 71 + n, device=DEV, poison=None)
+    g = torch.Generator().manual_seed(n)
+    ints = lambda t: torch.randint(-4, 5, t.shape, generator=g).to(DEV).float()
+    inp.q = ints(inp.q).to(inp.q.dtype)
+    inp.k_cache = (ints(inp.k_cache) * (1.0 if kv == "fp8" else scale)).to(inp.k_cache.dtype)
+    if kv == "fp8":
+        inp.k_scale.fill_(scale)
+    out, lse = run_verify(inp)
+    ref_o, ref_l = oracle_verify(inp)
+    eo, el = max_err(out, ref_o), lse_err(lse, ref_l)
+    print(f"  max|out-oracle|={eo:.3e} max|lse-oracle|={el:.3e} max|lse|={np.abs(ref_l).max():.0f}", flush=True)
+    assert eo <= TOL32 and el <= TOL32 + np.abs(ref_l).max() * 2.0 ** -21

@@ -31,6 +31,8 @@
 // 2.88 ms on the generic vector kernel, 90 us with fp32 products, 70 us with the
 // split (5.2 TB/s, of which the start of the launch is 6-8 us); fp32 K/V at
 // head_dim 128, 512-2048 keys (0.58 GB): 120 us.
+#include <type_traits>
+
 #include "mfma_common.h"
 
 namespace spire {
@@ -147,7 +149,26 @@ template <int D, int NB> struct State32 {
     f32x4 acc[D / 16][NB];
     float l[NB], msub[NB], thr[NB];
     int lim[NB];
+    bool far;  // a reference of kFastReference or more (lazy_softmax)
 };
+
+// Two forms of the softmax.  The fast one (lazy_softmax) takes the exact product
+// s * sc less a rounded reference, so the probability at the maximum is 2^(rounding
+// error of the reference): near 1 below 2^20 (half an ulp is 2^-5), 0 or infinite
+// from 2^31 on.  And its reference lags the maximum, so that sums of values near the
+// end of the range overflow, while an infinite value times a zero lower term of its
+// probability is NaN where the product with the whole probability is infinite.  A
+// range with a reference of 2^20 or more, or with an accumulator that is not finite
+// (none becomes finite again), is therefore computed again by the careful form.
+// References are lowered by kLift: the hardware exponential drops results below
+// 2^-126, which is then 2^-150 of the reference, as little as fp32 holds at all.
+constexpr float kFastReference = 0x1p20f;
+constexpr float kLift = 24.f, kUnlift = 0x1p-24f;
+// An element that calls for the careful form (8-bit values: 448 at most).
+template <int ES> __device__ __forceinline__ bool overflowed(f32x4 o) {
+    if constexpr (ES == 1) return false;
+    else return !(max3n(fabsf(o[0]), fabsf(o[1]), __builtin_elementwise_maximum(fabsf(o[2]), fabsf(o[3]))) < INFINITY);
+}
 
 // V^T operands of dim block mb (dims 4m + mb) for the bf16 PV product: element t
 // = 4g + i of lane (m, j) is key 16g + 4j + i.
@@ -183,9 +204,105 @@ __device__ __forceinline__ void split3(float p, uint32_t &hi, uint32_t &mid, uin
 // the upper halves of two words
 __device__ __forceinline__ uint32_t upper2(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
 
-// SPLIT: the PV product on the bf16 instruction, every probability as its three
-// bf16 terms; else on the fp32 instruction.
-template <int ES, int D, int NB, int KG, bool SPLIT>
+// The careful softmax of a tile: products s * sc rounded before the reference is
+// subtracted (exactly 0 at the maximum), the reference the maximum of all keys so
+// far, denormal probabilities kept, and accumulators that hold the weighted mean
+// of the values so far in place of their weighted sum, which no finite value can
+// make overflow.  l: the whole row sum, on every lane.
+template <int D, int NB, int KG>
+__device__ __forceinline__ void careful_softmax(f32x4 (&s)[KG][NB], State32<D, NB> &st, float sc) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int g = 0; g < KG; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s[g][nb][i] = mul_rounded(s[g][nb][i], sc);
+                mx = fmaxf(mx, s[g][nb][i]);
+            }
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float mold = st.thr[nb] == -INFINITY ? -INFINITY : st.msub[nb];
+        const float mnew = fmaxf(mold, mx);
+        const float msub = mnew == -INFINITY ? 0.f : mnew;
+        float l = 0.f;
+#pragma unroll
+        for (int g = 0; g < KG; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s[g][nb][i] = exp2f(s[g][nb][i] - msub);
+                l += s[g][nb][i];
+            }
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        const float old = st.l[nb] * exp2f(mold - msub);
+        l += old;
+        // l == 0: no visible key; l NaN: a NaN key or a +inf score was visible
+        const float inv = l > 0.f ? 1.f / l : l;
+#pragma unroll
+        for (int g = 0; g < KG; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[g][nb][i] *= inv;
+#pragma unroll
+        for (int mb = 0; mb < D / 16; ++mb) st.acc[mb][nb] *= old * inv;
+        st.l[nb] = l;
+        st.msub[nb] = msub;
+        st.thr[nb] = mnew == -INFINITY ? -INFINITY : 0.f;  // a reference exists
+    }
+}
+
+// The online softmax of a tile with a lazy reference maximum, as compute_tile
+// (mfma_common.h), lowered by kLift: sums and accumulators carry a factor 2^24.
+// l: this lane's part of the row sum.
+template <int D, int NB, int KG>
+__device__ __forceinline__ void lazy_softmax(f32x4 (&s)[KG][NB], State32<D, NB> &st, float sc) {
+    float lmax[NB];
+    bool over = false;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        if constexpr (KG == 2) {
+            lmax[nb] = max8(s[0][nb], s[1][nb]);
+        } else {
+            lmax[nb] = __builtin_elementwise_maximum(s[0][nb][0], max3n(s[0][nb][1], s[0][nb][2], s[0][nb][3]));
+        }
+        over |= lmax[nb] > st.thr[nb];
+    }
+    if (__any(over)) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            float mx = fmaxf(lmax[nb], __shfl_xor(lmax[nb], 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            mx *= sc;  // sc > 0
+            const float mold = st.thr[nb] == -INFINITY ? -INFINITY : st.msub[nb] + kLift;
+            const float mnew = mx > mold + kRescaleLog2 ? mx : mold;
+            const float ref = mnew == -INFINITY ? 0.f : mnew;
+            const float alpha = exp2f(mold - ref);  // 1 when unchanged, 0 from -inf
+            st.msub[nb] = ref - kLift;
+            st.far |= !(fabsf(ref) < kFastReference);
+            st.thr[nb] = mnew == -INFINITY ? -INFINITY : fmaxf((mnew + kRescaleLog2) / sc, -FLT_MAX);
+#pragma unroll
+            for (int mb = 0; mb < D / 16; ++mb) st.acc[mb][nb] *= alpha;
+            st.l[nb] *= alpha;
+        }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        float l = 0.f;
+#pragma unroll
+        for (int g = 0; g < KG; ++g) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[g][nb][i] = fast_exp2(fmaf(s[g][nb][i], sc, -st.msub[nb]));
+            l += (s[g][nb][0] + s[g][nb][1]) + (s[g][nb][2] + s[g][nb][3]);
+        }
+        st.l[nb] += l;
+    }
+}
+
+// FAST: the lazy reference maximum (careful_softmax otherwise), and for 16- and
+// 8-bit values the PV product on the bf16 instruction, every probability as its
+// three bf16 terms; else on the fp32 instruction.
+template <int ES, int D, int NB, int KG, bool FAST>
 __device__ __forceinline__ void compute_tile32(Tile32<ES, D, KG> &T, const Q32<ES, D, NB> &q, State32<D, NB> &st,
                                                int tile, int n, int full_lim, float sc, int lane) {
     using TT = Tile32<ES, D, KG>;
@@ -234,46 +351,8 @@ __device__ __forceinline__ void compute_tile32(Tile32<ES, D, KG> &T, const Q32<E
                 for (int i = 0; i < 4; ++i)
                     if (key0 + 16 * g + 4 * j + i >= st.lim[nb]) s[g][nb][i] = -INFINITY;
     }
-    // online softmax with a lazy reference maximum, as compute_tile (mfma_common.h)
-    float lmax[NB];
-    bool over = false;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        if constexpr (KG == 2) {
-            lmax[nb] = max8(s[0][nb], s[1][nb]);
-        } else {
-            lmax[nb] = __builtin_elementwise_maximum(s[0][nb][0], max3n(s[0][nb][1], s[0][nb][2], s[0][nb][3]));
-        }
-        over |= lmax[nb] > st.thr[nb];
-    }
-    if (__any(over)) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            float mx = fmaxf(lmax[nb], __shfl_xor(lmax[nb], 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            mx *= sc;  // sc > 0
-            const float mold = st.thr[nb] == -INFINITY ? -INFINITY : st.msub[nb];
-            const float mnew = mx > mold + kRescaleLog2 ? mx : mold;
-            const float msub = mnew == -INFINITY ? 0.f : mnew;
-            const float alpha = fast_exp2(mold - msub);  // 1 when unchanged, 0 from -inf
-            st.msub[nb] = msub;
-            st.thr[nb] = mnew == -INFINITY ? -INFINITY : fmaxf((mnew + kRescaleLog2) / sc, -FLT_MAX);
-#pragma unroll
-            for (int mb = 0; mb < D / 16; ++mb) st.acc[mb][nb] *= alpha;
-            st.l[nb] *= alpha;
-        }
-    }
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        float l = 0.f;
-#pragma unroll
-        for (int g = 0; g < KG; ++g) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[g][nb][i] = fast_exp2(fmaf(s[g][nb][i], sc, -st.msub[nb]));
-            l += (s[g][nb][0] + s[g][nb][1]) + (s[g][nb][2] + s[g][nb][3]);
-        }
-        st.l[nb] += l;
-    }
+    if constexpr (FAST) lazy_softmax<D, NB, KG>(s, st, sc);
+    else careful_softmax<D, NB, KG>(s, st, sc);
     if (key0 + 16 * KG > n) {  // uniform: storage of keys beyond the segment end may hold anything
 #pragma unroll
         for (int g = 0; g < KG; ++g)
@@ -284,8 +363,8 @@ __device__ __forceinline__ void compute_tile32(Tile32<ES, D, KG> &T, const Q32<E
                     for (int x = 0; x < TT::VW; ++x) T.v[g][i][x] = 0u;
                 }
     }
-    if constexpr (SPLIT) {
-        static_assert(D == 64 && KG == 2 && ES <= 2, "32 keys of 64 dims, 16-bit or 8-bit values");
+    if constexpr (FAST && ES <= 2) {
+        static_assert(D == 64 && KG == 2, "32 keys of 64 dims, 16-bit or 8-bit values");
         u32x4 a[4];
         value_bf16<ES>(T.v, a);
 #pragma unroll
@@ -325,6 +404,7 @@ template <int ES, int D, int NB>
 __device__ __forceinline__ void begin_rows32(const Problem &p, int b, int h, int n, int r0, Q32<ES, D, NB> &q,
                                              State32<D, NB> &st, int lane) {
     const int n16 = lane & 15, j = lane >> 4;
+    st.far = false;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int r = r0 + 16 * nb + n16;
@@ -362,30 +442,35 @@ template <int ES, int D> __device__ __forceinline__ int dim32(int i, int x, int 
     return ES == 4 ? 64 * x + 16 * j + 4 * i : 32 * j + 8 * i + 4 * x;
 }
 
-// Final rows (whole) or a partial into workspace slot `slot`.
-template <int ES, int D, int NB>
-__device__ __forceinline__ void end_rows32(const Problem &p, const Plan &pl, State32<D, NB> &st, int b, int h, int r0,
-                                           bool whole, int64_t slot, int lane) {
+// Final rows (whole) or a partial into workspace slot `slot` of the unit whose
+// rows start at u0.  MEAN: the accumulators hold means (stream32_careful).  True
+// where an accumulator of a row without NaN scores was not finite.
+template <int ES, int D, int NB, bool MEAN>
+__device__ __forceinline__ bool end_rows32(const Problem &p, const Plan &pl, State32<D, NB> &st, int b, int h, int r0,
+                                           int u0, bool whole, int64_t slot, int lane) {
     const int n16 = lane & 15, j = lane >> 4;
     const float vs = ES == 1 ? uload(p.kv.v_scale, h) : 1.f;
+    bool over = false;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         float l = st.l[nb];
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
+        if (!MEAN) l *= kUnlift;
         const int r = r0 + 16 * nb + n16;
         if (r >= p.R) continue;
         // l == 0: no visible key; l NaN: a NaN key or a +inf score was visible
-        const float inv = l > 0.f ? vs / l : (l == 0.f ? 0.f : l);
-        const float lse2 = l > 0.f ? st.msub[nb] + log2f(l) : (l == 0.f ? -INFINITY : l);
+        const float inv = l > 0.f ? (MEAN ? vs : vs / l) : (l == 0.f ? 0.f : l);
+        const float lse2 = l > 0.f ? (MEAN ? st.msub[nb] : st.msub[nb] + kLift) + log2f(l) : (l == 0.f ? -INFINITY : l);
         const int64_t off = row_offset(p, b, h, r);
-        float *part = pl.part_o + (slot * pl.rows + (r - r0)) * (int64_t)D;
+        float *part = pl.part_o + (slot * pl.rows + (r - u0)) * (int64_t)D;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int x = 0; x < D / 64; ++x) {
                 const f32x4 o = f32x4{st.acc[4 * x][nb][i], st.acc[4 * x + 1][nb][i], st.acc[4 * x + 2][nb][i],
-                                      st.acc[4 * x + 3][nb][i]} * inv;
+                                      st.acc[4 * x + 3][nb][i]} * (MEAN ? 1.f : kUnlift) * inv;
+                if constexpr (!MEAN) over |= overflowed<ES>(o) && l == l;
                 const int d = dim32<ES, D>(i, x, j);
                 if (!whole)
                     *reinterpret_cast<f32x4 *>(part + d) = o;
@@ -396,10 +481,11 @@ __device__ __forceinline__ void end_rows32(const Problem &p, const Plan &pl, Sta
                     *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(p.out) + off + d) = o;
             }
         if (j == 0) {
-            if (!whole) pl.part_lse[slot * pl.rows + (r - r0)] = lse2;
+            if (!whole) pl.part_lse[slot * pl.rows + (r - u0)] = lse2;
             else if (p.lse != nullptr) p.lse[lse_index(p, b, h, r)] = lse2 * 0.69314718055994531f;
         }
     }
+    return over;
 }
 
 // Tiles [first, last] through NBUF register buffers, NBUF - 1 tiles in flight:
@@ -413,43 +499,49 @@ __device__ __forceinline__ void stream32(const SegAddr &a, const Q32<ES, D, NB> 
 #pragma unroll
     for (int x = 0; x < NBUF - 1; ++x)
         if (first + x <= last) load_tile32<ES, D, KG, MODE, KNT>(T[x], a, first + x, lane);
-    int tt = first;
-    while (true) {
+    // One exit where the compiler otherwise keeps a set of accumulators per exit, for
+    // the check of their magnitude after it (head_dim 128, two blocks: scratch); three
+    // exits elsewhere (fp8 within 2 %, the other way 1.5 % slower).
+    if constexpr (ES == 4 || (ES == 2 && MODE == MODE_PAGED)) {
+        for (int tt = first; tt <= last; tt += NBUF) {
 #pragma unroll
-        for (int x = 0; x < NBUF; ++x) {
-            if (tt + NBUF - 1 <= last)
-                load_tile32<ES, D, KG, MODE, KNT>(T[(x + NBUF - 1) % NBUF], a, tt + NBUF - 1, lane);
-            compute_tile32<ES, D, NB, KG, ES <= 2>(T[x], q, st, tt, n, full_lim, sc, lane);
-            if (++tt > last) return;
+            for (int x = 0; x < NBUF; ++x) {
+                if (tt + x + NBUF - 1 <= last)
+                    load_tile32<ES, D, KG, MODE, KNT>(T[(x + NBUF - 1) % NBUF], a, tt + x + NBUF - 1, lane);
+                if (x == 0 || tt + x <= last)
+                    compute_tile32<ES, D, NB, KG, true>(T[x], q, st, tt + x, n, full_lim, sc, lane);
+            }
+        }
+        if constexpr (ES == 4) settle(st.acc);
+    } else {
+        int tt = first;
+        while (true) {
+#pragma unroll
+            for (int x = 0; x < NBUF; ++x) {
+                if (tt + NBUF - 1 <= last)
+                    load_tile32<ES, D, KG, MODE, KNT>(T[(x + NBUF - 1) % NBUF], a, tt + NBUF - 1, lane);
+                compute_tile32<ES, D, NB, KG, true>(T[x], q, st, tt, n, full_lim, sc, lane);
+                if (++tt > last) return;
+            }
         }
     }
 }
 
-// An infinite value times a zero lower term of its probability is NaN where the
-// product with the whole probability is infinite.  Rare: a range whose outputs
-// hold a NaN that its row sums do not is computed again with fp32 products.
-template <int ES, int D, int NB>
-__device__ __forceinline__ bool lost_infinity(const State32<D, NB> &st) {
-    bool nan = false;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        bool x = false;
-#pragma unroll
-        for (int mb = 0; mb < D / 16; ++mb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) x |= st.acc[mb][nb][i] != st.acc[mb][nb][i];
-        nan |= x && st.l[nb] == st.l[nb];
-    }
-    return __any(nan);
-}
-template <int ES, int D, int NB, int KG, int MODE>
-__device__ __forceinline__ void stream32_exact(const SegAddr &a, const Q32<ES, D, NB> &q, State32<D, NB> &st,
-                                                         int first, int last, int n, int full_lim, float sc, int lane) {
+// Rows r0 .. r0 + 15 over the same tiles by the careful form, one tile at a time
+// (rare): the accumulators are left as means, the row sums on one lane group.
+template <int ES, int D, int KG, int MODE>
+__device__ __forceinline__ void stream32_careful(const Problem &p, const SegAddr &a, State32<D, 1> &st, int b, int h,
+                                                 int r0, int first, int last, int n, int full_lim, float sc, int lane) {
+    Q32<ES, D, 1> q;
+    begin_rows32<ES, D, 1>(p, b, h, n, r0, q, st, lane);
+#pragma nounroll
     for (int tt = first; tt <= last; ++tt) {
         Tile32<ES, D, KG> T;
         load_tile32<ES, D, KG, MODE>(T, a, tt, lane);
-        compute_tile32<ES, D, NB, KG, false>(T, q, st, tt, n, full_lim, sc, lane);
+        compute_tile32<ES, D, 1, KG, false>(T, q, st, tt, n, full_lim, sc, lane);
+        settle(st.acc);
     }
+    if ((lane >> 4) != 0) st.l[0] = 0.f;
 }
 
 template <int ES, int D, int NB, int MODE>
@@ -496,16 +588,19 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_partial_kernel(Pr
             begin_rows32<ES, D, NB>(p, b, h, n, r0, q, st, lane);
             float sc = p.sm_scale_log2;
             if (ES == 1) sc *= uload(p.kv.k_scale, h);
-            if (n > 0) {
-                const int full_lim = p.draft ? n : n - p.k;
-                stream32<ES, D, NB, KG, MODE>(a, q, st, tile, t1 - 1, n, full_lim, sc, lane);
-                if (ES <= 2 && lost_infinity<ES, D, NB>(st)) {
-                    begin_rows32<ES, D, NB>(p, b, h, n, r0, q, st, lane);
-                    stream32_exact<ES, D, NB, KG, MODE>(a, q, st, tile, t1 - 1, n, full_lim, sc, lane);
+            const int full_lim = p.draft ? n : n - p.k;
+            const bool whole = tile == 0 && t1 == tiles_b;
+            const int64_t slot = 2 * (int64_t)wid + (pos == begin ? 0 : 1);
+            if (n > 0) stream32<ES, D, NB, KG, MODE>(a, q, st, tile, t1 - 1, n, full_lim, sc, lane);
+            const bool over = end_rows32<ES, D, NB, false>(p, pl, st, b, h, r0, r0, whole, slot, lane);
+            if (__any(st.far || over)) {  // the same lanes write the rows again
+#pragma nounroll
+                for (int r = r0; r < r0 + 16 * NB && r < p.R; r += 16) {
+                    State32<D, 1> one;
+                    stream32_careful<ES, D, KG, MODE>(p, a, one, b, h, r, tile, t1 - 1, n, full_lim, sc, lane);
+                    end_rows32<ES, D, 1, true>(p, pl, one, b, h, r, r0, whole, slot, lane);
                 }
             }
-            end_rows32<ES, D, NB>(p, pl, st, b, h, r0, tile == 0 && t1 == tiles_b,
-                                  2 * (int64_t)wid + (pos == begin ? 0 : 1), lane);
         }
         pos += te - tile;
         ++seg;
@@ -528,6 +623,7 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kerne
     __shared__ f32x4 s_o[SPW][G > 1 ? G : 1][G > 1 ? NS : 1][64];
     __shared__ float s_l[SPW][G][16];
     __shared__ float s_m[SPW][G][16];  // reference maximum; -inf: none
+    __shared__ bool s_mean[SPW][G];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n16 = lane & 15, j = lane >> 4;
@@ -536,69 +632,72 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kerne
     const bool valid = seg < p.B * p.Hkv;
     const int b = valid ? seg / p.Hkv : 0;
     const int h = valid ? seg - b * p.Hkv : 0;
-    State32<D, 1> st;
-    if (valid) {
-        const int n = effective_keys(p, b);
-        const int T = (n + 16 * KG - 1) / (16 * KG);
-        const int t0 = part * T / G, t1 = (part + 1) * T / G;
-        Q32<ES, D, 1> q;
-        begin_rows32<ES, D, 1>(p, b, h, n, 0, q, st, lane);
-        float sc = p.sm_scale_log2;
-        if (ES == 1) sc *= uload(p.kv.k_scale, h);
-        if (t0 < t1) {
-            const SegAddr a = make_seg_addr<MODE_DRAFT>(p, b, h, n);
-            // a segment with a CU to itself: ordinary K loads (ld16k; bf16, head_dim 64, 104
-            // segments of 1024 keys 13.9 -> 12.8 us; the 64-sequence verify call loses 3 %)
-            stream32<ES, D, 1, KG, MODE_DRAFT, G != 4>(a, q, st, t0, t1 - 1, n, n, sc, lane);
-            if (ES <= 2 && lost_infinity<ES, D, 1>(st)) {
-                begin_rows32<ES, D, 1>(p, b, h, n, 0, q, st, lane);
-                stream32_exact<ES, D, 1, KG, MODE_DRAFT>(a, q, st, t0, t1 - 1, n, n, sc, lane);
-            }
-        }
-    }
-    if constexpr (G == 1) {  // nothing to merge
-        if (valid) end_rows32<ES, D, 1>(p, Plan{}, st, b, h, 0, true, 0, lane);
-    } else {
-        if (valid) {
+    // what a wave found: the rows themselves (G = 1), or its part in LDS; as end_rows32
+    auto leave = [&](State32<D, 1> &st, auto mean_tag) -> bool {
+        constexpr bool MEAN = decltype(mean_tag)::value;
+        if constexpr (G == 1) {
+            return end_rows32<ES, D, 1, MEAN>(p, Plan{}, st, b, h, 0, 0, true, 0, lane);
+        } else {
             float l = st.l[0];
             l += __shfl_xor(l, 16);
             l += __shfl_xor(l, 32);
             if (j == 0) {
-                s_l[slot][part][n16] = l;
-                s_m[slot][part][n16] = st.thr[0] == -INFINITY ? -INFINITY : st.msub[0];
+                s_l[slot][part][n16] = MEAN ? l : l * kUnlift;
+                s_m[slot][part][n16] = st.thr[0] == -INFINITY ? -INFINITY : (MEAN ? st.msub[0] : st.msub[0] + kLift);
+                if (n16 == 0) s_mean[slot][part] = MEAN;
             }
+            bool over = false;
 #pragma unroll
             for (int y = 0; y < NS; ++y) {
                 const int i = y & 3, x = y >> 2;
-                s_o[slot][part][y][lane] = f32x4{st.acc[4 * x][0][i], st.acc[4 * x + 1][0][i], st.acc[4 * x + 2][0][i],
-                                                 st.acc[4 * x + 3][0][i]};
+                const f32x4 o = f32x4{st.acc[4 * x][0][i], st.acc[4 * x + 1][0][i], st.acc[4 * x + 2][0][i],
+                                      st.acc[4 * x + 3][0][i]} * (MEAN ? 1.f : kUnlift);
+                if constexpr (!MEAN) over |= overflowed<ES>(o) && l == l;
+                s_o[slot][part][y][lane] = o;
             }
+            return over;
         }
+    };
+    if (valid) {
+        const int n = effective_keys(p, b);
+        const int T = (n + 16 * KG - 1) / (16 * KG);
+        const int t0 = part * T / G, t1 = (part + 1) * T / G;
+        State32<D, 1> st;
+        Q32<ES, D, 1> q;
+        begin_rows32<ES, D, 1>(p, b, h, n, 0, q, st, lane);
+        float sc = p.sm_scale_log2;
+        if (ES == 1) sc *= uload(p.kv.k_scale, h);
+        const SegAddr a = make_seg_addr<MODE_DRAFT>(p, b, h, n);
+        // a segment with a CU to itself: ordinary K loads (ld16k; bf16, head_dim 64, 104
+        // segments of 1024 keys 13.9 -> 12.8 us; the 64-sequence verify call loses 3 %)
+        if (t0 < t1) stream32<ES, D, 1, KG, MODE_DRAFT, G != 4>(a, q, st, t0, t1 - 1, n, n, sc, lane);
+        const bool over = leave(st, std::false_type{});
+        if (__any(st.far || over)) {  // the same lanes leave it again
+            State32<D, 1> one;
+            stream32_careful<ES, D, KG, MODE_DRAFT>(p, a, one, b, h, 0, t0, t1 - 1, n, n, sc, lane);
+            leave(one, std::true_type{});
+        }
+    }
+    if constexpr (G > 1) {
         __syncthreads();
         if (!valid || n16 >= p.R) return;
-        float wgt[G], M = -INFINITY, l = 0.f;
+        float m[G], l[G];
 #pragma unroll
         for (int w = 0; w < G; ++w) {
-            wgt[w] = s_m[slot][w][n16];
-            M = fmaxf(M, wgt[w]);
+            m[w] = s_m[slot][w][n16];
+            l[w] = s_l[slot][w][n16];
         }
-        M = M == -INFINITY ? 0.f : M;
+        RowMerge<G> mr = merge_row<G>(m, l, ES == 1 ? uload(p.kv.v_scale, h) : 1.f);
 #pragma unroll
-        for (int w = 0; w < G; ++w) {
-            wgt[w] = wgt[w] == -INFINITY ? 0.f : exp2f(wgt[w] - M);
-            l += s_l[slot][w][n16] * wgt[w];
-        }
-        // l == 0: no visible key; l NaN: a NaN key or a +inf score was visible
-        const float vs = ES == 1 ? uload(p.kv.v_scale, h) : 1.f;
-        const float inv = l > 0.f ? vs / l : (l == 0.f ? 0.f : l);
+        for (int w = 0; w < G; ++w)
+            if (s_mean[slot][w]) mr.w[w] *= l[w];
         const int64_t off = row_offset(p, b, h, n16);
 #pragma unroll
         for (int z = 0; z < PER; ++z) {
             const int y = part * PER + z;
             f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int w = 0; w < G; ++w) o += s_o[slot][w][y][lane] * wgt[w];
-            o *= inv;
+            for (int w = 0; w < G; ++w) o += s_o[slot][w][y][lane] * mr.w[w];
             const int d = dim32<ES, D>(y & 3, y >> 2, j);
             if (p.out_dtype == SPIRE_BF16)
                 *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + off + d) =
@@ -606,10 +705,7 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kerne
             else
                 *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(p.out) + off + d) = o;
         }
-        if (part == 0 && j == 0 && p.lse != nullptr) {
-            const float lse2 = l > 0.f ? M + log2f(l) : (l == 0.f ? -INFINITY : l);
-            p.lse[lse_index(p, b, h, n16)] = lse2 * 0.69314718055994531f;
-        }
+        if (part == 0 && j == 0 && p.lse != nullptr) p.lse[lse_index(p, b, h, n16)] = mr.lse2 * 0.69314718055994531f;
     }
 }
 

@@ -694,4 +694,31 @@ __device__ __forceinline__ void end_rows(const Problem &p, const Plan &pl, Softm
     }
 }
 
+// ---- merge of one row's parts left in LDS by the G waves of a segment ------------
+// m: each wave's reference maximum (-inf: none; its zero or NaN sums still
+// propagate), l: its row sum, vs: the value scale.  w: the factors of the waves'
+// accumulators, the row's division included, so that a merged sum is a mean and
+// overflows only where a wave's own sum did.  Denormal weights are kept, as in the
+// combine.
+template <int G> struct RowMerge { float w[G], lse2; };
+template <int G>
+__device__ __forceinline__ RowMerge<G> merge_row(const float (&m)[G], const float (&l)[G], float vs) {
+    RowMerge<G> r;
+    float M = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < G; ++w) M = fmaxf(M, m[w]);
+    M = M == -INFINITY ? 0.f : M;
+#pragma unroll
+    for (int w = 0; w < G; ++w) {
+        r.w[w] = m[w] == -INFINITY ? 0.f : exp2f(m[w] - M);
+        sum += l[w] * r.w[w];
+    }
+    // 0: no visible key; NaN: a NaN key or a +inf score was visible
+    const float inv = sum > 0.f ? vs / sum : (sum == 0.f ? 0.f : sum);
+#pragma unroll
+    for (int w = 0; w < G; ++w) r.w[w] *= inv;
+    r.lse2 = sum > 0.f ? M + log2f(sum) : (sum == 0.f ? -INFINITY : sum);
+    return r;
+}
+
 }  // namespace spire

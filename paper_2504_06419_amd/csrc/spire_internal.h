@@ -162,6 +162,13 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
     return (uint16_t)(u >> 16);
 }
 
+// a * b rounded to fp32, whatever follows: the compiler fuses an ordinary product
+// (__fmul_rn is one) with a sum or difference of it.
+__device__ __forceinline__ float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+
 // ---- host-side launchers (one per kernel family) ---------------------------
 hipError_t launch_plan(const Problem &p, const Plan &pl, hipStream_t st);
 hipError_t launch_mfma_partial(const Problem &p, const Plan &pl, int nb, hipStream_t st);

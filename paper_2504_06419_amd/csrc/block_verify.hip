@@ -62,7 +62,7 @@ __device__ __forceinline__ double block_prefix_weights(const TokenProblem &t, in
 
 // Weight of one entry of row i: residual p32 * P - Q (Q given) or P.
 __device__ __forceinline__ uint64_t block_weight(float scale, float pv, const float *qrow, int x) {
-    return fixed_weight(qrow ? __fsub_rn(__fmul_rn(scale, pv), qrow[x]) : pv);
+    return fixed_weight(qrow ? mul_rounded(scale, pv) - qrow[x] : pv);
 }
 
 // h_i = S / (S + (1 - p) 2^40) in fp64, S converted with one rounding (its
@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kTvThreads) void block_weights_kernel(TokenProblem 
     for (int g = 0; g < kTvGroupsPerLane; ++g) {
         if (resid) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sw += fixed_weight(__fsub_rn(__fmul_rn(scale, pv[g][e]), qv[g][e]));
+            for (int e = 0; e < 4; ++e) sw += fixed_weight(mul_rounded(scale, pv[g][e]) - qv[g][e]);
         } else {
             sw += fixed_weight(pv[g].x) + fixed_weight(pv[g].y) + fixed_weight(pv[g].z) + fixed_weight(pv[g].w);
         }
@@ -142,7 +142,7 @@ __device__ __forceinline__ void block_select_in_piece(const float *prow, const f
 #pragma unroll
     for (int e = 0; e < kTvSlice; ++e) {
         // entries past cnt hold 0 and weigh 0 either way
-        w[e] = fixed_weight(qrow ? __fsub_rn(__fmul_rn(scale, pv[e]), qv[e]) : pv[e]);
+        w[e] = fixed_weight(qrow ? mul_rounded(scale, pv[e]) - qv[e] : pv[e]);
         sum += w[e];
     }
     uint64_t total;

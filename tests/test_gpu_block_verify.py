@@ -140,3 +140,27 @@ def test_block_verify_is_deterministic_and_records_launches():
     spire.block_verify(p, q, d, ua, us, opts=rec.opts())
     names = [nm for nm, ms in rec.collect()]
     assert names == ["block_weights", "block_select"]
+
+
+@pytest.mark.parametrize("V", [7, 4099, 8192])
+def test_residual_rounds_its_product(V):
+    """A residual entry is w32 * p rounded, less q: q is that rounded product here,
+    so entries that are 0 would hold the product's rounding error if both
+    operations were one.  Even sequences: a row of such entries only, which has no
+    mass and cannot stop the walk (u = 0); odd ones: one entry of mass behind them,
+    which is the token drawn with u = 0."""
+    banner(f"block verify: residual products rounded, V={V}")
+    B, k = 8, 2
+    rng = np.random.default_rng(V)
+    p = rng.random((B, k + 1, V), dtype=np.float32) / V
+    q = rng.random((B, k, V), dtype=np.float32) / V
+    draft = np.zeros((B, k), np.int32)
+    p[:, 0, 0], q[:, 0, 0] = 0.3 / V, 0.7 / V
+    w32 = np.float32(np.float64(p[0, 0, 0]) / np.float64(q[0, 0, 0]))
+    q[:, 1, :] = w32 * p[:, 1, :]
+    assert ((w32.astype(np.float64) * p[:, 1].astype(np.float64)) > q[:, 1]).any(axis=1).all()
+    q[1::2, 1, V - 1] = 0.0                       # odd: the last entry keeps its mass
+    draft[:, 1] = -1                              # w_2 = 0: the walk stops at row 1 or 0
+    args = [torch.from_numpy(a).to(DEV) for a in (p, q, draft, np.zeros((B, k), np.float32), np.zeros(B, np.float32))]
+    n, tok = _compare(args)
+    assert (n[::2] == 0).all() and (n[1::2] == 1).all() and (tok[1::2, 1] == V - 1).all()

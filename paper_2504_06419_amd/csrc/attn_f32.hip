@@ -149,25 +149,49 @@ template <int D, int NB> struct State32 {
     f32x4 acc[D / 16][NB];
     float l[NB], msub[NB], thr[NB];
     int lim[NB];
-    bool far;  // a reference of kFastReference or more (lazy_softmax)
+    // what a range calls for the careful form by (needs_care)
+    bool far;            // a reference of kFastReference or more
+    float top;           // 32-bit values: the largest magnitude
+    f16x2 vmax, vmin;    // 16-bit values, both halves of their words
 };
 
 // Two forms of the softmax.  The fast one (lazy_softmax) takes the exact product
 // s * sc less a rounded reference, so the probability at the maximum is 2^(rounding
 // error of the reference): near 1 below 2^20 (half an ulp is 2^-5), 0 or infinite
-// from 2^31 on.  And its reference lags the maximum, so that sums of values near the
-// end of the range overflow, while an infinite value times a zero lower term of its
-// probability is NaN where the product with the whole probability is infinite.  A
-// range with a reference of 2^20 or more, or with an accumulator that is not finite
-// (none becomes finite again), is therefore computed again by the careful form.
-// References are lowered by kLift: the hardware exponential drops results below
-// 2^-126, which is then 2^-150 of the reference, as little as fp32 holds at all.
-constexpr float kFastReference = 0x1p20f;
-constexpr float kLift = 24.f, kUnlift = 0x1p-24f;
-// An element that calls for the careful form (8-bit values: 448 at most).
-template <int ES> __device__ __forceinline__ bool overflowed(f32x4 o) {
-    if constexpr (ES == 1) return false;
-    else return !(max3n(fabsf(o[0]), fabsf(o[1]), __builtin_elementwise_maximum(fabsf(o[2]), fabsf(o[3]))) < INFINITY);
+// from 2^31 on.  Its reference lags the maximum, so that sums of values near the end
+// of the range overflow; a probability below 2^-126 is dropped, which such a value
+// would make up for; and an infinite value times a zero lower term of its probability
+// is NaN where the product with the whole probability is infinite.  A range with a
+// reference of 2^20 or more, or a value of 2^65 or more (infinities and NaN
+// included), is therefore computed again by the careful form.
+// The values are looked at in half an instruction per 32-bit word, and in one per
+// word of two 16-bit ones: as fp16 patterns, whose order is that of the bits, so
+// that 2^65 is 512 and what is NaN there is larger still (the maximum and minimum
+// keep NaN).
+constexpr float kFastReference = 0x1p20f, kFastValue = 0x1p65f;
+template <int ES, int D, int NB, int N>
+__device__ __forceinline__ void note_values(State32<D, NB> &st, const uint32_t (&w)[N]) {
+    static_assert(N % 2 == 0 || ES == 1, "words in pairs");
+    if constexpr (ES == 1) return;  // 448 at most
+#pragma unroll
+    for (int x = 0; x + 1 < N; x += 2) {
+        if constexpr (ES == 4) {
+            st.top = max3n(st.top, fabsf(__uint_as_float(w[x])), fabsf(__uint_as_float(w[x + 1])));
+        } else {
+            const f16x2 a = __builtin_bit_cast(f16x2, w[x]), b = __builtin_bit_cast(f16x2, w[x + 1]);
+            st.vmax = __builtin_elementwise_maximum(__builtin_elementwise_maximum(st.vmax, a), b);
+            st.vmin = __builtin_elementwise_minimum(__builtin_elementwise_minimum(st.vmin, a), b);
+        }
+    }
+}
+template <int ES, int D, int NB> __device__ __forceinline__ bool needs_care(const State32<D, NB> &st) {
+    bool care = st.far;
+    if constexpr (ES == 4) care |= !(st.top < kFastValue);
+    if constexpr (ES == 2) {
+        const _Float16 most = (_Float16)512.f;  // bits 0x6000: 2^65 in bf16
+        care |= !(st.vmax.x < most) || !(st.vmax.y < most) || !(st.vmin.x > -most) || !(st.vmin.y > -most);
+    }
+    return __any(care);
 }
 
 // V^T operands of dim block mb (dims 4m + mb) for the bf16 PV product: element t
@@ -253,8 +277,7 @@ __device__ __forceinline__ void careful_softmax(f32x4 (&s)[KG][NB], State32<D, N
 }
 
 // The online softmax of a tile with a lazy reference maximum, as compute_tile
-// (mfma_common.h), lowered by kLift: sums and accumulators carry a factor 2^24.
-// l: this lane's part of the row sum.
+// (mfma_common.h).  l: this lane's part of the row sum.
 template <int D, int NB, int KG>
 __device__ __forceinline__ void lazy_softmax(f32x4 (&s)[KG][NB], State32<D, NB> &st, float sc) {
     float lmax[NB];
@@ -274,12 +297,12 @@ __device__ __forceinline__ void lazy_softmax(f32x4 (&s)[KG][NB], State32<D, NB> 
             float mx = fmaxf(lmax[nb], __shfl_xor(lmax[nb], 16));
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             mx *= sc;  // sc > 0
-            const float mold = st.thr[nb] == -INFINITY ? -INFINITY : st.msub[nb] + kLift;
+            const float mold = st.thr[nb] == -INFINITY ? -INFINITY : st.msub[nb];
             const float mnew = mx > mold + kRescaleLog2 ? mx : mold;
-            const float ref = mnew == -INFINITY ? 0.f : mnew;
-            const float alpha = exp2f(mold - ref);  // 1 when unchanged, 0 from -inf
-            st.msub[nb] = ref - kLift;
-            st.far |= !(fabsf(ref) < kFastReference);
+            const float msub = mnew == -INFINITY ? 0.f : mnew;
+            const float alpha = fast_exp2(mold - msub);  // 1 when unchanged, 0 from -inf
+            st.msub[nb] = msub;
+            st.far |= !(fabsf(msub) < kFastReference);
             st.thr[nb] = mnew == -INFINITY ? -INFINITY : fmaxf((mnew + kRescaleLog2) / sc, -FLT_MAX);
 #pragma unroll
             for (int mb = 0; mb < D / 16; ++mb) st.acc[mb][nb] *= alpha;
@@ -363,6 +386,14 @@ __device__ __forceinline__ void compute_tile32(Tile32<ES, D, KG> &T, const Q32<E
                     for (int x = 0; x < TT::VW; ++x) T.v[g][i][x] = 0u;
                 }
     }
+    if constexpr (FAST) {
+#pragma unroll
+        for (int g = 0; g < KG; ++g) {
+            if constexpr (TT::VW == 1) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) note_values<ES>(st, T.v[g][i]);
+        }
+    }
     if constexpr (FAST && ES <= 2) {
         static_assert(D == 64 && KG == 2, "32 keys of 64 dims, 16-bit or 8-bit values");
         u32x4 a[4];
@@ -405,6 +436,8 @@ __device__ __forceinline__ void begin_rows32(const Problem &p, int b, int h, int
                                              State32<D, NB> &st, int lane) {
     const int n16 = lane & 15, j = lane >> 4;
     st.far = false;
+    st.top = 0.f;
+    st.vmax = st.vmin = f16x2{(_Float16)0.f, (_Float16)0.f};
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int r = r0 + 16 * nb + n16;
@@ -443,25 +476,22 @@ template <int ES, int D> __device__ __forceinline__ int dim32(int i, int x, int 
 }
 
 // Final rows (whole) or a partial into workspace slot `slot` of the unit whose
-// rows start at u0.  MEAN: the accumulators hold means (stream32_careful).  True
-// where an accumulator of a row without NaN scores was not finite.
+// rows start at u0.  MEAN: the accumulators hold means (stream32_careful).
 template <int ES, int D, int NB, bool MEAN>
-__device__ __forceinline__ bool end_rows32(const Problem &p, const Plan &pl, State32<D, NB> &st, int b, int h, int r0,
+__device__ __forceinline__ void end_rows32(const Problem &p, const Plan &pl, State32<D, NB> &st, int b, int h, int r0,
                                            int u0, bool whole, int64_t slot, int lane) {
     const int n16 = lane & 15, j = lane >> 4;
     const float vs = ES == 1 ? uload(p.kv.v_scale, h) : 1.f;
-    bool over = false;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         float l = st.l[nb];
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
-        if (!MEAN) l *= kUnlift;
         const int r = r0 + 16 * nb + n16;
         if (r >= p.R) continue;
         // l == 0: no visible key; l NaN: a NaN key or a +inf score was visible
         const float inv = l > 0.f ? (MEAN ? vs : vs / l) : (l == 0.f ? 0.f : l);
-        const float lse2 = l > 0.f ? (MEAN ? st.msub[nb] : st.msub[nb] + kLift) + log2f(l) : (l == 0.f ? -INFINITY : l);
+        const float lse2 = l > 0.f ? st.msub[nb] + log2f(l) : (l == 0.f ? -INFINITY : l);
         const int64_t off = row_offset(p, b, h, r);
         float *part = pl.part_o + (slot * pl.rows + (r - u0)) * (int64_t)D;
 #pragma unroll
@@ -469,8 +499,7 @@ __device__ __forceinline__ bool end_rows32(const Problem &p, const Plan &pl, Sta
 #pragma unroll
             for (int x = 0; x < D / 64; ++x) {
                 const f32x4 o = f32x4{st.acc[4 * x][nb][i], st.acc[4 * x + 1][nb][i], st.acc[4 * x + 2][nb][i],
-                                      st.acc[4 * x + 3][nb][i]} * (MEAN ? 1.f : kUnlift) * inv;
-                if constexpr (!MEAN) over |= overflowed<ES>(o) && l == l;
+                                      st.acc[4 * x + 3][nb][i]} * inv;
                 const int d = dim32<ES, D>(i, x, j);
                 if (!whole)
                     *reinterpret_cast<f32x4 *>(part + d) = o;
@@ -485,7 +514,6 @@ __device__ __forceinline__ bool end_rows32(const Problem &p, const Plan &pl, Sta
             else if (p.lse != nullptr) p.lse[lse_index(p, b, h, r)] = lse2 * 0.69314718055994531f;
         }
     }
-    return over;
 }
 
 // Tiles [first, last] through NBUF register buffers, NBUF - 1 tiles in flight:
@@ -499,29 +527,16 @@ __device__ __forceinline__ void stream32(const SegAddr &a, const Q32<ES, D, NB> 
 #pragma unroll
     for (int x = 0; x < NBUF - 1; ++x)
         if (first + x <= last) load_tile32<ES, D, KG, MODE, KNT>(T[x], a, first + x, lane);
-    // One exit where the compiler otherwise keeps a set of accumulators per exit, for
-    // the check of their magnitude after it (head_dim 128, two blocks: scratch); three
-    // exits elsewhere (fp8 within 2 %, the other way 1.5 % slower).
-    if constexpr (ES == 4 || (ES == 2 && MODE == MODE_PAGED)) {
-        for (int tt = first; tt <= last; tt += NBUF) {
+    int tt = first;
+    while (true) {
 #pragma unroll
-            for (int x = 0; x < NBUF; ++x) {
-                if (tt + x + NBUF - 1 <= last)
-                    load_tile32<ES, D, KG, MODE, KNT>(T[(x + NBUF - 1) % NBUF], a, tt + x + NBUF - 1, lane);
-                if (x == 0 || tt + x <= last)
-                    compute_tile32<ES, D, NB, KG, true>(T[x], q, st, tt + x, n, full_lim, sc, lane);
-            }
-        }
-        if constexpr (ES == 4) settle(st.acc);
-    } else {
-        int tt = first;
-        while (true) {
-#pragma unroll
-            for (int x = 0; x < NBUF; ++x) {
-                if (tt + NBUF - 1 <= last)
-                    load_tile32<ES, D, KG, MODE, KNT>(T[(x + NBUF - 1) % NBUF], a, tt + NBUF - 1, lane);
-                compute_tile32<ES, D, NB, KG, true>(T[x], q, st, tt, n, full_lim, sc, lane);
-                if (++tt > last) return;
+        for (int x = 0; x < NBUF; ++x) {
+            if (tt + NBUF - 1 <= last)
+                load_tile32<ES, D, KG, MODE, KNT>(T[(x + NBUF - 1) % NBUF], a, tt + NBUF - 1, lane);
+            compute_tile32<ES, D, NB, KG, true>(T[x], q, st, tt, n, full_lim, sc, lane);
+            if (++tt > last) {
+                if constexpr (ES == 4) settle(st.acc);
+                return;
             }
         }
     }
@@ -592,8 +607,9 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_partial_kernel(Pr
             const bool whole = tile == 0 && t1 == tiles_b;
             const int64_t slot = 2 * (int64_t)wid + (pos == begin ? 0 : 1);
             if (n > 0) stream32<ES, D, NB, KG, MODE>(a, q, st, tile, t1 - 1, n, full_lim, sc, lane);
-            const bool over = end_rows32<ES, D, NB, false>(p, pl, st, b, h, r0, r0, whole, slot, lane);
-            if (__any(st.far || over)) {  // the same lanes write the rows again
+            if (!needs_care<ES>(st)) {
+                end_rows32<ES, D, NB, false>(p, pl, st, b, h, r0, r0, whole, slot, lane);
+            } else {
 #pragma nounroll
                 for (int r = r0; r < r0 + 16 * NB && r < p.R; r += 16) {
                     State32<D, 1> one;
@@ -632,30 +648,26 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kerne
     const bool valid = seg < p.B * p.Hkv;
     const int b = valid ? seg / p.Hkv : 0;
     const int h = valid ? seg - b * p.Hkv : 0;
-    // what a wave found: the rows themselves (G = 1), or its part in LDS; as end_rows32
-    auto leave = [&](State32<D, 1> &st, auto mean_tag) -> bool {
+    // what a wave found: the rows themselves (G = 1), or its part in LDS
+    auto leave = [&](State32<D, 1> &st, auto mean_tag) {
         constexpr bool MEAN = decltype(mean_tag)::value;
         if constexpr (G == 1) {
-            return end_rows32<ES, D, 1, MEAN>(p, Plan{}, st, b, h, 0, 0, true, 0, lane);
+            end_rows32<ES, D, 1, MEAN>(p, Plan{}, st, b, h, 0, 0, true, 0, lane);
         } else {
             float l = st.l[0];
             l += __shfl_xor(l, 16);
             l += __shfl_xor(l, 32);
             if (j == 0) {
-                s_l[slot][part][n16] = MEAN ? l : l * kUnlift;
-                s_m[slot][part][n16] = st.thr[0] == -INFINITY ? -INFINITY : (MEAN ? st.msub[0] : st.msub[0] + kLift);
+                s_l[slot][part][n16] = l;
+                s_m[slot][part][n16] = st.thr[0] == -INFINITY ? -INFINITY : st.msub[0];
                 if (n16 == 0) s_mean[slot][part] = MEAN;
             }
-            bool over = false;
 #pragma unroll
             for (int y = 0; y < NS; ++y) {
                 const int i = y & 3, x = y >> 2;
-                const f32x4 o = f32x4{st.acc[4 * x][0][i], st.acc[4 * x + 1][0][i], st.acc[4 * x + 2][0][i],
-                                      st.acc[4 * x + 3][0][i]} * (MEAN ? 1.f : kUnlift);
-                if constexpr (!MEAN) over |= overflowed<ES>(o) && l == l;
-                s_o[slot][part][y][lane] = o;
+                s_o[slot][part][y][lane] = f32x4{st.acc[4 * x][0][i], st.acc[4 * x + 1][0][i], st.acc[4 * x + 2][0][i],
+                                                 st.acc[4 * x + 3][0][i]};
             }
-            return over;
         }
     };
     if (valid) {
@@ -671,8 +683,9 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kerne
         // a segment with a CU to itself: ordinary K loads (ld16k; bf16, head_dim 64, 104
         // segments of 1024 keys 13.9 -> 12.8 us; the 64-sequence verify call loses 3 %)
         if (t0 < t1) stream32<ES, D, 1, KG, MODE_DRAFT, G != 4>(a, q, st, t0, t1 - 1, n, n, sc, lane);
-        const bool over = leave(st, std::false_type{});
-        if (__any(st.far || over)) {  // the same lanes leave it again
+        if (!needs_care<ES>(st)) {
+            leave(st, std::false_type{});
+        } else {
             State32<D, 1> one;
             stream32_careful<ES, D, KG, MODE_DRAFT>(p, a, one, b, h, 0, t0, t1 - 1, n, n, sc, lane);
             leave(one, std::true_type{});
@@ -688,9 +701,14 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kerne
             l[w] = s_l[slot][w][n16];
         }
         RowMerge<G> mr = merge_row<G>(m, l, ES == 1 ? uload(p.kv.v_scale, h) : 1.f);
+        bool mean = false;
 #pragma unroll
-        for (int w = 0; w < G; ++w)
-            if (s_mean[slot][w]) mr.w[w] *= l[w];
+        for (int w = 0; w < G; ++w) mean |= s_mean[slot][w];
+        if (mean) {  // a mean's weight takes its sum, the division first: no term beyond the largest value
+#pragma unroll
+            for (int w = 0; w < G; ++w) mr.w[w] *= mr.inv * (s_mean[slot][w] ? l[w] : 1.f);
+            mr.inv = 1.f;
+        }
         const int64_t off = row_offset(p, b, h, n16);
 #pragma unroll
         for (int z = 0; z < PER; ++z) {
@@ -698,6 +716,7 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kerne
             f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int w = 0; w < G; ++w) o += s_o[slot][w][y][lane] * mr.w[w];
+            o *= mr.inv;
             const int d = dim32<ES, D>(y & 3, y >> 2, j);
             if (p.out_dtype == SPIRE_BF16)
                 *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + off + d) =

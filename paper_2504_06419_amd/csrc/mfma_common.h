@@ -696,11 +696,11 @@ __device__ __forceinline__ void end_rows(const Problem &p, const Plan &pl, Softm
 
 // ---- merge of one row's parts left in LDS by the G waves of a segment ------------
 // m: each wave's reference maximum (-inf: none; its zero or NaN sums still
-// propagate), l: its row sum, vs: the value scale.  w: the factors of the waves'
-// accumulators, the row's division included, so that a merged sum is a mean and
-// overflows only where a wave's own sum did.  Denormal weights are kept, as in the
+// propagate), l: its row sum, vs: the value scale.  w: the weights of the waves'
+// accumulators, at most 1 / G each, so that their sum overflows only where a
+// wave's own did; inv: the factor of the sum.  Denormal weights are kept, as in the
 // combine.
-template <int G> struct RowMerge { float w[G], lse2; };
+template <int G> struct RowMerge { float w[G], inv, lse2; };
 template <int G>
 __device__ __forceinline__ RowMerge<G> merge_row(const float (&m)[G], const float (&l)[G], float vs) {
     RowMerge<G> r;
@@ -710,14 +710,12 @@ __device__ __forceinline__ RowMerge<G> merge_row(const float (&m)[G], const floa
     M = M == -INFINITY ? 0.f : M;
 #pragma unroll
     for (int w = 0; w < G; ++w) {
-        r.w[w] = m[w] == -INFINITY ? 0.f : exp2f(m[w] - M);
+        r.w[w] = exp2f(m[w] - M) * (1.f / G);  // 0 from -inf
         sum += l[w] * r.w[w];
     }
     // 0: no visible key; NaN: a NaN key or a +inf score was visible
-    const float inv = sum > 0.f ? vs / sum : (sum == 0.f ? 0.f : sum);
-#pragma unroll
-    for (int w = 0; w < G; ++w) r.w[w] *= inv;
-    r.lse2 = sum > 0.f ? M + log2f(sum) : (sum == 0.f ? -INFINITY : sum);
+    r.inv = sum > 0.f ? vs / sum : (sum == 0.f ? 0.f : sum);
+    r.lse2 = sum > 0.f ? M + log2f(sum * G) : (sum == 0.f ? -INFINITY : sum);
     return r;
 }
 

@@ -1,7 +1,7 @@
 """Finite extremes on the calls of the fp32 matrix path (head_dim 64, and fp32
 K/V): scores of 1e10, scores on both sides of 2^20 (where the path turns from its
 fast to its careful form), values of 1e37, both, and a few such values among
-ordinary ones, in segments of one worker and of many, next to ordinary sequences.
+ordinary ones or behind weights that only denormal numbers hold, in segments of one worker and of many, next to ordinary sequences.
 
 Scores: query and key entries are small integers times a power of two, so every
 score is exact in fp32 in any order of summation and two different scores differ
@@ -23,6 +23,11 @@ DEV = "cuda"
 TOL32 = 1e-5
 KINDS = [("f32", 64), ("f32", 128), ("bf16", 64), ("fp8", 64)]
 BIG_V = 2.0 ** 123
+
+
+def _cases(scores, values):
+    """fp8 values do not exceed 448: scores only."""
+    return [(kv, D, what) for kv, D in KINDS for what in scores + (values if kv != "fp8" else [])]
 
 
 def _grid(t, seed, scale):
@@ -59,12 +64,9 @@ def _extreme_scores(q, k, k_scale, seed, even=2.0 ** 15):
 
 
 # one worker a segment, one segment over many workers, several segments a worker
-@pytest.mark.parametrize("kv,D", KINDS)
+@pytest.mark.parametrize("kv,D,what", _cases(["scores", "edge"], ["values", "both", "few", "faint"]))
 @pytest.mark.parametrize("B,Hkv,lo,hi,ps", [(3, 2, 40, 300, 0), (1, 2, 9000, 9000, 16), (300, 8, 1, 60, 16)])
-@pytest.mark.parametrize("what", ["scores", "edge", "values", "both", "few"])
 def test_verify(kv, D, B, Hkv, lo, hi, ps, what):
-    if kv == "fp8" and what not in ("scores", "edge"):
-        pytest.skip("fp8 values do not exceed 448")
     banner(f"extremes verify {kv} D={D} B={B} ctx=[{lo},{hi}] ps={ps}: {what}")
     spec = W.VerifySpec(B=B, Hq=4 * Hkv, Hkv=Hkv, D=D, k=2, ctx_lo=lo, ctx_hi=hi, kv_dtype=kv,
                         q_dtype="f32" if kv == "f32" else "bf16", page_size=ps)
@@ -81,18 +83,21 @@ def test_verify(kv, D, B, Hkv, lo, hi, ps, what):
         row = inp.v_cache[int(inp.block_table[0, 0]) if ps else 0]   # the first keys of sequence 0
         row[:, 3:6] = _grid(row[:, 3:6], 19, BIG_V)
         vscale = BIG_V
+    elif what == "faint":   # the same values behind weights of e^-90, which make up about 1e-2 / the row sum
+        blk = int(inp.block_table[0, 0]) if ps else 0
+        inp.q[..., 0] = 64.0
+        inp.k_cache[..., 0] = torch.where(inp.k_cache[..., 0].isnan(), inp.k_cache[..., 0], 0.0)
+        inp.k_cache[blk, :, 3:6, 0] = -90.0 * D ** 0.5 / 64.0
+        inp.v_cache[blk, :, 3:6] = _grid(inp.v_cache[blk, :, 3:6], 19, BIG_V)
     ids = list(range(B)) if B < 10 else [0, 1, 2, 150, 151, 298, 299]
     out, lse = run_verify(inp)
     _check(out[ids], lse[ids], oracle_verify(inp, ids), vscale)
 
 
 # whole segments with four, two and one wave each; the partition; more than 16 rows
-@pytest.mark.parametrize("kv,D", KINDS)
+@pytest.mark.parametrize("kv,D,what", _cases(["scores"], ["values", "both"]))
 @pytest.mark.parametrize("B,g,kernel", [(9, 4, 0), (280, 4, 0), (600, 4, 0), (9, 4, 2), (9, 24, 0)])
-@pytest.mark.parametrize("what", ["scores", "values", "both"])
 def test_draft(kv, D, B, g, kernel, what):
-    if kv == "fp8" and what != "scores":
-        pytest.skip("fp8 values do not exceed 448")
     banner(f"extremes draft {kv} D={D} B={B} g={g} kernel={kernel}: {what}")
     spec = W.DraftSpec(B=B, Hq=g, Hkv=1, D=D, S=4, W=124 if B < 100 else 52, steps=1, ctx_lo=20, ctx_hi=400,
                        kv_dtype=kv, q_dtype="f32" if kv == "f32" else "bf16")

@@ -209,19 +209,20 @@ __global__ __launch_bounds__(256, 1) void mfma_draft_coop_kernel(Problem p) {
 #pragma unroll
         for (int w = 0; w < G - 1; ++w) M = fmaxf(M, s_m[slot][w][nb][lane]);
         M = M == -INFINITY ? 0.f : M;
-        const float a0 = m0 == -INFINITY ? 0.f : fast_exp2(m0 - M);
+        // weights of at most 1 / G, denormal ones kept, as in merge_row
+        const float a0 = m0 == -INFINITY ? 0.f : exp2f(m0 - M) * (1.f / G);
         l *= a0;
 #pragma unroll
         for (int mb = 0; mb < 8; ++mb) st.acc[mb][nb] *= a0;
 #pragma unroll
         for (int w = 0; w < G - 1; ++w) {
             const float mw = s_m[slot][w][nb][lane];
-            const float aw = mw == -INFINITY ? 0.f : fast_exp2(mw - M);
+            const float aw = mw == -INFINITY ? 0.f : exp2f(mw - M) * (1.f / G);
             l += s_l[slot][w][nb][lane] * aw;
 #pragma unroll
             for (int mb = 0; mb < 8; ++mb) st.acc[mb][nb] += s_acc[slot][w][mb * NB + nb][lane] * aw;
         }
-        st.msub[nb] = M;
+        st.msub[nb] = M + (G == 4 ? 2.f : 1.f);
         // end_rows sums the four lane groups' partial row sums: one holds it all
         st.l[nb] = (lane >> 4) == 0 ? l : 0.f;
     }
@@ -301,38 +302,28 @@ __global__ __launch_bounds__(64 * G, G / 4) void mfma_draft_short_kernel(Problem
     for (int nb = 0; nb < NB; ++nb) {
         const int r = 16 * nb + n16;
         if (r >= p.R) continue;
-        float wgt[G], M = -INFINITY, l = 0.f;
+        float m[G], l[G];
 #pragma unroll
         for (int w = 0; w < G; ++w) {
-            wgt[w] = s_m[w][nb][n16];
-            M = fmaxf(M, wgt[w]);
+            m[w] = s_m[w][nb][n16];
+            l[w] = s_l[w][nb][n16];
         }
-        M = M == -INFINITY ? 0.f : M;
-#pragma unroll
-        for (int w = 0; w < G; ++w) {
-            wgt[w] = wgt[w] == -INFINITY ? 0.f : fast_exp2(wgt[w] - M);
-            l += s_l[w][nb][n16] * wgt[w];
-        }
-        // l == 0: no visible key; l NaN: a NaN key or a +inf score was visible
-        const float inv = l > 0.f ? vs / l : (l == 0.f ? 0.f : l);
+        const RowMerge<G> mr = merge_row<G>(m, l, vs);
         const int64_t off = row_offset(p, b, h, r) + 32 * j;
 #pragma unroll
         for (int y = 0; y < SPW; ++y) {
             const int x = part * SPW + y;
             f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int w = 0; w < G; ++w) o += s_o[w][nb][x][lane] * wgt[w];
-            o *= inv;
+            for (int w = 0; w < G; ++w) o += s_o[w][nb][x][lane] * mr.w[w];
+            o *= mr.inv;
             if (p.out_dtype == SPIRE_BF16)
                 *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(p.out) + off + 4 * x) =
                     u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
             else
                 *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(p.out) + off + 4 * x) = o;
         }
-        if (part == 0 && j == 0 && p.lse != nullptr) {
-            const float lse2 = l > 0.f ? M + log2f(l) : (l == 0.f ? -INFINITY : l);
-            p.lse[lse_index(p, b, h, r)] = lse2 * 0.69314718055994531f;
-        }
+        if (part == 0 && j == 0 && p.lse != nullptr) p.lse[lse_index(p, b, h, r)] = mr.lse2 * 0.69314718055994531f;
     }
 }
 

@@ -11,7 +11,7 @@ import torch
 from paper_2504_06419_amd import spire
 from paper_2504_06419_amd import workloads as W
 from tests.gpu_helpers import banner
-from tests.test_gpu_draft_coop import _check
+from tests.test_gpu_draft_coop import _check, _run
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -133,3 +133,21 @@ def test_fp32_path_degenerate_lengths_and_nonfinite(kv_dtype, D, B):
     assert torch.isnan(out[0]).all() and torch.isnan(out[1]).all()
     assert torch.isinf(out[2]).all()
     assert (out[3:6] == 0).all() and torch.isneginf(lse[3:6]).all()
+
+
+# one workgroup a segment (one and two row blocks), two waves a segment
+@pytest.mark.parametrize("B,g", [(9, 4), (9, 24), (280, 4)])
+def test_merge_does_not_overflow(B, g):
+    """128 equal weights on values of 2^121: the values of one wave sum to at most
+    2^127, those of the segment to 2^128.  The partition's partials are means."""
+    banner(f"short segments: merge of large values B={B} g={g}")
+    inp = _inputs(B, 1, "bf16", g, 4, 124, 500, 500, 5700 + B)
+    inp.q[0].zero_()
+    inp.ring_v.fill_(2.0 ** 121)
+    inp.sink_v.fill_(2.0 ** 121)
+    rec = spire.LaunchRecorder(4)
+    for kernel, names in ((0, ["draft_partial"]), (2, ["draft_partial", "combine"])):
+        out, _ = _run(inp, inp.seq_lens(0), kernel, rec)
+        assert [nm for nm, _ in rec.collect()] == names
+        print(f"  kernel {kernel}: least {float(out.min()):.6e} largest {float(out.max()):.6e}", flush=True)
+        assert float((out / 2.0 ** 121 - 1).abs().max()) <= TOL32

@@ -150,8 +150,7 @@ template <int D, int NB> struct State32 {
     float l[NB], msub[NB], thr[NB];
     int lim[NB];
     // what a range calls for the careful form by (needs_care)
-    bool far;            // a reference of kFastReference or more
-    float top;           // 32-bit values: the largest magnitude
+    float top;           // infinite: a reference of kFastReference or more; 32-bit values: the largest magnitude
     f16x2 vmax, vmin;    // 16-bit values, both halves of their words
 };
 
@@ -185,8 +184,7 @@ __device__ __forceinline__ void note_values(State32<D, NB> &st, const uint32_t (
     }
 }
 template <int ES, int D, int NB> __device__ __forceinline__ bool needs_care(const State32<D, NB> &st) {
-    bool care = st.far;
-    if constexpr (ES == 4) care |= !(st.top < kFastValue);
+    bool care = !(st.top < kFastValue);
     if constexpr (ES == 2) {
         const _Float16 most = (_Float16)512.f;  // bits 0x6000: 2^65 in bf16
         care |= !(st.vmax.x < most) || !(st.vmax.y < most) || !(st.vmin.x > -most) || !(st.vmin.y > -most);
@@ -302,7 +300,7 @@ __device__ __forceinline__ void lazy_softmax(f32x4 (&s)[KG][NB], State32<D, NB> 
             const float msub = mnew == -INFINITY ? 0.f : mnew;
             const float alpha = fast_exp2(mold - msub);  // 1 when unchanged, 0 from -inf
             st.msub[nb] = msub;
-            st.far |= !(fabsf(msub) < kFastReference);
+            st.top = fabsf(msub) < kFastReference ? st.top : INFINITY;
             st.thr[nb] = mnew == -INFINITY ? -INFINITY : fmaxf((mnew + kRescaleLog2) / sc, -FLT_MAX);
 #pragma unroll
             for (int mb = 0; mb < D / 16; ++mb) st.acc[mb][nb] *= alpha;
@@ -331,11 +329,13 @@ __device__ __forceinline__ void compute_tile32(Tile32<ES, D, KG> &T, const Q32<E
     using TT = Tile32<ES, D, KG>;
     const int j = lane >> 4;
     const int key0 = tile * 16 * KG;
-    f32x4 s[KG][NB];
+    // fp32 products: two sums of half the terms each, with less rounding than one (the
+    // second in the registers of the keys the first is done with)
+    f32x4 s[KG][NB], s1[KG][NB];
 #pragma unroll
     for (int g = 0; g < KG; ++g)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) s[g][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < NB; ++nb) s[g][nb] = s1[g][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < TT::NKC; ++c) {
         if constexpr (ES == 4) {
@@ -344,8 +344,10 @@ __device__ __forceinline__ void compute_tile32(Tile32<ES, D, KG> &T, const Q32<E
 #pragma unroll
                 for (int g = 0; g < KG; ++g)
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        s[g][nb] = mfma_f32(__uint_as_float(T.k[g][c][e]), __uint_as_float(q.r[nb][c][e]), s[g][nb]);
+                    for (int nb = 0; nb < NB; ++nb) {
+                        f32x4 &sum = 2 * c >= TT::NKC ? s1[g][nb] : s[g][nb];
+                        sum = mfma_f32(__uint_as_float(T.k[g][c][e]), __uint_as_float(q.r[nb][c][e]), sum);
+                    }
         } else if constexpr (ES == 2) {
 #pragma unroll
             for (int g = 0; g < KG; ++g)
@@ -364,7 +366,14 @@ __device__ __forceinline__ void compute_tile32(Tile32<ES, D, KG> &T, const Q32<E
             }
         }
     }
-    if constexpr (ES == 4) settle(s);
+    if constexpr (ES == 4) {
+        settle(s);
+        settle(s1);
+#pragma unroll
+        for (int g = 0; g < KG; ++g)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) s[g][nb] += s1[g][nb];
+    }
     if (key0 + 16 * KG > full_lim) {  // uniform: only tiles reaching past a row's last visible key
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
@@ -435,7 +444,6 @@ template <int ES, int D, int NB>
 __device__ __forceinline__ void begin_rows32(const Problem &p, int b, int h, int n, int r0, Q32<ES, D, NB> &q,
                                              State32<D, NB> &st, int lane) {
     const int n16 = lane & 15, j = lane >> 4;
-    st.far = false;
     st.top = 0.f;
     st.vmax = st.vmin = f16x2{(_Float16)0.f, (_Float16)0.f};
 #pragma unroll
@@ -516,6 +524,17 @@ __device__ __forceinline__ void end_rows32(const Problem &p, const Plan &pl, Sta
     }
 }
 
+// The tile's key registers hold nothing from here on (no instruction; without it
+// the compiler keeps them where no next tile is loaded).  fp32 drafts of many short
+// segments run three waves per SIMD with it (162 registers, 170 without: 2400
+// segments of 64 keys 20.3 us, 21.3).
+template <int ES, int D, int KG> __device__ __forceinline__ void forget_keys(Tile32<ES, D, KG> &T) {
+#pragma unroll
+    for (int g = 0; g < KG; ++g)
+#pragma unroll
+        for (int c = 0; c < Tile32<ES, D, KG>::NKC; ++c) asm volatile("" : "=v"(T.k[g][c]));
+}
+
 // Tiles [first, last] through NBUF register buffers, NBUF - 1 tiles in flight:
 // three, and five of the 4 KB fp8 tiles while they fit (64 sequences of 512-8192
 // fp8 keys, 20 rows: 57.6 -> 52.4 us; bf16 within 1 % from two to five).
@@ -533,6 +552,8 @@ __device__ __forceinline__ void stream32(const SegAddr &a, const Q32<ES, D, NB> 
         for (int x = 0; x < NBUF; ++x) {
             if (tt + NBUF - 1 <= last)
                 load_tile32<ES, D, KG, MODE, KNT>(T[(x + NBUF - 1) % NBUF], a, tt + NBUF - 1, lane);
+            else if constexpr (ES == 4 && MODE == MODE_DRAFT)
+                forget_keys(T[(x + NBUF - 1) % NBUF]);
             compute_tile32<ES, D, NB, KG, true>(T[x], q, st, tt, n, full_lim, sc, lane);
             if (++tt > last) {
                 if constexpr (ES == 4) settle(st.acc);
@@ -677,6 +698,7 @@ __global__ __launch_bounds__(64 * kMfmaWavesPerWG, 1) void f32_draft_whole_kerne
         State32<D, 1> st;
         Q32<ES, D, 1> q;
         begin_rows32<ES, D, 1>(p, b, h, n, 0, q, st, lane);
+        st.lim[0] = n;  // a draft's rows see every key: uniform
         float sc = p.sm_scale_log2;
         if (ES == 1) sc *= uload(p.kv.k_scale, h);
         const SegAddr a = make_seg_addr<MODE_DRAFT>(p, b, h, n);

@@ -163,3 +163,19 @@ def test_scores_of_hundreds_and_thousands(kv, D, n, scale):
     eo, el = max_err(out, ref_o), lse_err(lse, ref_l)
     print(f"  max|out-oracle|={eo:.3e} max|lse-oracle|={el:.3e} max|lse|={np.abs(ref_l).max():.0f}", flush=True)
     assert eo <= TOL32 and el <= TOL32 + np.abs(ref_l).max() * 2.0 ** -21
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,Hkv,g,W_,lo,hi", [(96, 8, 2, 248, 249, 529), (5, 1, 8, 1884, 83, 341), (12, 2, 4, 60, 100, 200)])
+def test_no_further_from_64_bits_than_the_vector_kernel(D, B, Hkv, g, W_, lo, hi):
+    """fp32 K/V: the matrix kernels' sums round no more than those of the vector
+    kernel, in the 2-norm over all outputs of the same inputs."""
+    banner(f"fp32 path: error against 64 bits D={D} B={B} W={W_}")
+    spec = W.DraftSpec(B=B, Hq=g * Hkv, Hkv=Hkv, D=D, S=4, W=W_, steps=1, ctx_lo=lo, ctx_hi=hi, kv_dtype="f32", q_dtype="f32")
+    inp = W.make_draft_inputs(spec, 81 + B, device=DEV)
+    W.write_step_token(inp, 0)
+    ref = oracle_draft(inp, 0)[0]
+    err = [float(np.linalg.norm(run_draft(inp, 0, kernel=kernel)[0].double().cpu().numpy() - ref) / np.linalg.norm(ref))
+           for kernel in (0, 1)]
+    print(f"  matrix {err[0]:.2e} vector {err[1]:.2e}", flush=True)
+    assert err[0] <= err[1]

@@ -142,6 +142,40 @@ def test_nonfinite_keys_and_draft_values():
     assert np.array_equal(np.isnan(g), np.isnan(ref_o)) and np.isnan(ref_o).any()
 
 
+# the merge's forms with the check in the same launch: a workgroup per worker, per
+# segment without and with groups of threads; one and two units per KV head
+@pytest.mark.parametrize("kv,D,k,g,B,Hkv", [("bf16", 64, 3, 4, 200, 8), ("f32", 64, 3, 4, 200, 8), ("bf16", 64, 4, 4, 64, 8),
+                                            ("fp8", 64, 4, 4, 64, 8), ("f32", 64, 8, 8, 3, 2), ("f32", 128, 8, 8, 3, 2),
+                                            ("bf16", 64, 15, 8, 3, 2), ("f32", 64, 8, 8, 60, 8), ("f32", 64, 8, 8, 40, 16)])
+def test_nonfinite_values_under_the_mask_in_every_merge(kv, D, k, g, B, Hkv):
+    """Every third sequence holds a NaN (not fp8: and an infinity) at keys that only
+    later rows see; every row against the oracle, and the other sequences' bits as
+    without them."""
+    banner(f"fp32 path: non-finite tails {kv} D={D} k={k} g={g} B={B} Hkv={Hkv}")
+    spec = W.VerifySpec(B=B, Hq=Hkv * g, Hkv=Hkv, D=D, k=k, ctx_lo=40, ctx_hi=6000 if B < 10 else 900, kv_dtype=kv,
+                        q_dtype="f32" if kv == "f32" else "bf16")
+    inp = W.make_verify_inputs(spec, 61 + B + k, device=DEV)
+    clean, _ = run_verify(inp)
+    n = inp.kv_lens.tolist()
+    v = inp.v_cache.view(torch.uint8) if kv == "fp8" else inp.v_cache
+    for b in range(0, B, 3):
+        h = (b // 3) % Hkv
+        v[b, h, n[b] - 1 - (b // 3) % k, (7 * b) % D] = 0x7F if kv == "fp8" else float("nan")
+        if kv != "fp8":
+            v[b, (h + 1) % Hkv, n[b] - 1, (5 * b + 1) % D] = float("inf")
+    out, lse = run_verify(inp)
+    ref_o, ref_l = oracle_verify(inp)
+    got = out.double().cpu().numpy()
+    assert np.array_equal(np.isnan(got), np.isnan(ref_o)) and np.array_equal(np.isposinf(got), np.isposinf(ref_o))
+    fin = np.isfinite(ref_o)
+    assert np.array_equal(np.isfinite(got), fin) and not fin.all() and np.isnan(ref_o).any()
+    eo = float(np.max(np.abs(got[fin] - ref_o[fin])))
+    print(f"  {B * Hkv} segments, {int((~fin).sum())} non-finite outputs, max|out-oracle|={eo:.3e}", flush=True)
+    assert eo <= TOL32 and lse_err(lse, ref_l) <= TOL32
+    rest = [b for b in range(B) if b % 3]
+    assert torch.equal(out[rest], clean[rest])
+
+
 @pytest.mark.parametrize("kv,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("fp8", 64)])
 @pytest.mark.parametrize("n,scale", [(60, 2.0 ** 6), (60, 2.0 ** 10), (3000, 2.0 ** 10)])
 def test_scores_of_hundreds_and_thousands(kv, D, n, scale):

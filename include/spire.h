@@ -134,6 +134,10 @@ size_t spire_verify_workspace_size(int32_t B, int32_t Hq, int32_t Hkv, int32_t D
  * row whose visible scores are all -inf is an empty row.  Storage outside a
  * row's visible keys never influences that row, whatever it holds -- also
  * keys [n_b - k + i, n_b), which only later rows see.
+ * Finite extremes: values up to 2^80 in magnitude never overflow, larger ones
+ * where sums of them do.  Scores may have any size, except that bf16 and fp8 K/V
+ * at head_dim 128 with bf16 queries need them below 2^20 in magnitude: beyond, a
+ * row can come out empty or NaN.
  */
 spire_status spire_verify_attn(const void *q, int32_t q_dtype, const spire_kv *kv,
                                const int32_t *kv_lens, int32_t B, int32_t Hq, int32_t Hkv,
@@ -185,7 +189,7 @@ size_t spire_draft_workspace_size(int32_t B, int32_t Hq, int32_t Hkv, int32_t D)
  *   ring_offset [B] int32, reduced modulo W on the device.
  *   sizes    S >= 0, W >= 0, S + W >= 1, other sizes as for verify with k = 0.
  *   out      [B, Hq, D]; lse [B, Hq] or NULL; workspace as for verify.
- * Non-finite values in visible positions act as for verify.
+ * Non-finite and very large values in visible positions act as for verify.
  */
 spire_status spire_draft_sparse_attn(const void *q, int32_t q_dtype, const spire_kv *sink,
                                      const spire_kv *ring, const int32_t *seq_lens,
@@ -387,17 +391,24 @@ int32_t spire_version(void);
  *   kernel        attention family (the token and block verification entry
  *                 points ignore it):
  *                 0 automatic -- the matrix-core kernels where dtype and shape
- *                 allow (LDS-staged above 32 rows per KV head, register-staged
- *                 otherwise, the fp32 ones at head_dim 64 and for fp32 K/V),
- *                 the generic vector kernel for the rest;
- *                 a draft step whose B * Hkv segments number half or a
- *                 quarter of the device's waves (4 per compute unit; at least
- *                 15/16 of them filled) gives each segment 2 or 4 waves of one
- *                 workgroup and launches no plan or combine;
- *                 1 always the generic vector kernel; 2 prefer the
- *                 register-staged kernel (at most 32 rows) with the stream-K
- *                 partition of every call; 3 prefer the LDS-staged one (bf16
- *                 K/V only above 32 rows); each where its limits allow.
+ *                 allow: for bf16 queries on bf16 or fp8 K/V at head_dim 128
+ *                 LDS-staged above 32 rows per KV head and register-staged
+ *                 otherwise; the fp32 ones for fp32 K/V, and for bf16 queries
+ *                 at head_dim 64; the generic vector kernel for the rest.
+ *                 A draft step launches one kernel, no plan and no combine,
+ *                 when each of its B * Hkv segments goes whole to one
+ *                 workgroup (up to 32 rows, fp32 kernels 16): short segments
+ *                 in any number -- with one per compute unit at most 240 KB of
+ *                 K+V (S + W keys) plus 1 KB per segment of the call, with
+ *                 more 192 to 256 KB on two waves each and 64 to 192 KB on one,
+ *                 by how full that leaves the device, an fp8 segment counting
+ *                 twice on the fp32 kernels -- and on the bf16 kernels also
+ *                 longer ones that number half or a quarter of the device's
+ *                 waves (4 per compute unit; at least 15/16 of them filled).
+ *                 1 always the generic vector kernel; 2 the stream-K partition
+ *                 of every call, on the register-staged kernel up to 32 rows and
+ *                 on the fp32 kernels; 3 prefer the LDS-staged kernel (bf16 K/V
+ *                 only above 32 rows); each where its limits allow.
  *                 Results agree within the stated tolerances; the choice
  *                 exists for measurement and cross-checks.
  *   max_launches  capacity of the two arrays below; 0 records nothing.

@@ -256,8 +256,8 @@ __global__ __launch_bounds__(64) void generic_partial_kernel(Problem p, Plan pl)
 // In the matrix-core kernels the rows that mask such a key still multiply its
 // value by a zero probability, and 0 * inf or 0 * NaN is NaN: a non-finite
 // value there (e.g. fp8 0x7F written for a NaN) would reach rows that must not
-// see it.  This pass, launched after the combine of a matrix-core verify call,
-// checks those few value rows of every (sequence, KV head); a segment holding a
+// see it.  This pass, launched after the combine of a bf16 matrix-core verify call
+// and with it on the fp32 path (combine_check_kernel), checks those few value rows of every (sequence, KV head); a segment holding a
 // non-finite one (rare) has all its rows recomputed here by the fp32 unit loop
 // above, which only accumulates a value for the rows that see its key, and
 // overwritten.  Its cost otherwise is reading k value rows per segment.

@@ -111,12 +111,7 @@ size_t workspace_bytes_for(int B, int R, int D) {
     }
     const Layout a = layout(B, R, D, w);
     const Layout b = layout(B, kGenericRowBlock, D, generic_workers(cus));
-    size_t total = std::max(a.total, b.total);
-    for (int elem : {1, 4}) {
-        if (elem != 4 && D != 64) continue;  // 16-bit and 8-bit K/V: head_dim 64 only
-        total = std::max(total, layout(B, f32_shape(R, elem, D).rows, D, mfma_workers(cus)).total);
-    }
-    return total;
+    return std::max(a.total, b.total);  // the fp32 kernels: mfma_workers, never more than R rows
 }
 
 // ---- per-call options: kernel family and launch events ----------------------------

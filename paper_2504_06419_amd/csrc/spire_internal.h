@@ -4,7 +4,8 @@
 //   * the keys of sequence b are cut into tiles of `tile` keys; a sequence
 //     with no key still owns one (empty) tile so that its rows get written;
 //   * a segment is one (sequence b, unit u) pair, where a unit is one KV head
-//     (matrix-core kernels) or one KV head x 16-row block (generic kernel);
+//     (bf16 matrix-core kernels), one KV head x up to 80 rows (fp32 matrix-core
+//     kernels) or one KV head x 16-row block (generic kernel);
 //     segment s = b * units + u owns tiles_b + seg_cost consecutive positions:
 //     its tiles followed by seg_cost phantom positions that stand for the
 //     fixed cost of a segment (queries, output rows, address set-up), so that
@@ -172,9 +173,9 @@ __device__ __forceinline__ float mul_rounded(float a, float b) {
 // ---- host-side launchers (one per kernel family) ---------------------------
 hipError_t launch_plan(const Problem &p, const Plan &pl, hipStream_t st);
 hipError_t launch_mfma_partial(const Problem &p, const Plan &pl, int nb, hipStream_t st);
-// Draft steps with whole segments per workgroup (g = 2 or 4 waves per segment):
+// Draft steps with whole segments per workgroup (g = 1, 2 or 4 waves per segment):
 // final rows written directly, no plan and no combine.
-// kDraftShort: the kernel for few, short segments.
+// kDraftShort: the kernel for few, short segments (8 waves, 4 beyond 16 rows).
 constexpr int kDraftShort = -1;
 hipError_t launch_mfma_draft_coop(const Problem &p, int nb, int g, hipStream_t st);
 hipError_t launch_generic_partial(const Problem &p, const Plan &pl, hipStream_t st);
@@ -190,9 +191,13 @@ constexpr int staged_wps(bool fp8, int nb) { return fp8 && nb > 2 && nb < 5 ? 2 
 int staged_workers(int cus, int nb, bool fp8);
 hipError_t launch_combine(const Problem &p, const Plan &pl, hipStream_t st);
 // fp32 matrix kernel (attn_f32.hip): keys per tile, the most row blocks of a
-// unit (what fits the registers beside three tiles; more rows are split evenly
-// over units, each of which reads the keys again), and the combine that includes
-// the check of the values of keys [n - k, n) (attn_generic.hip).
+// unit (more rows are split evenly over units, each of which reads the keys
+// again), and the combine that includes the check of the values of keys [n - k, n)
+// (attn_generic.hip).  The limits for fp32 K/V are not those of the registers:
+// one more unit suits small calls (4 sequences of 512 keys, 72 rows at head_dim
+// 64: 25.3 us on two units, 34.6 on one of five blocks), larger ones run faster on
+// one (64 of 512-2048 keys, 72 rows: 168 and 142; 32 of 48 rows at head_dim 128:
+// 132 and 102 with three blocks).
 constexpr int f32_tile(int elem) { return elem == 4 ? 16 : 32; }
 constexpr int f32_blocks(int elem, int D) { return elem < 4 ? 5 : (D == 64 ? 3 : 2); }
 struct F32Shape { int nb, units_per_head, rows; };

@@ -166,7 +166,9 @@ template <int D, int NB> struct State32 {
 // The values are looked at in half an instruction per 32-bit word, and in one per
 // word of two 16-bit ones: as fp16 patterns, whose order is that of the bits, so
 // that 2^65 is 512 and what is NaN there is larger still (the maximum and minimum
-// keep NaN).
+// keep NaN).  64 sequences, 20 rows, us a call in a graph without and with both
+// checks: bf16 73.4 / 73.9, fp8 60.2 / 60.6, fp32 head_dim 64 75.3 / 77.8, 128
+// 128.9 / 132.3.
 constexpr float kFastReference = 0x1p20f, kFastValue = 0x1p65f;
 template <int ES, int D, int NB, int N>
 __device__ __forceinline__ void note_values(State32<D, NB> &st, const uint32_t (&w)[N]) {

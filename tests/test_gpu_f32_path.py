@@ -213,3 +213,43 @@ def test_no_further_from_64_bits_than_the_vector_kernel(D, B, Hkv, g, W_, lo, hi
            for kernel in (0, 1)]
     print(f"  matrix {err[0]:.2e} vector {err[1]:.2e}", flush=True)
     assert err[0] <= err[1]
+
+
+def _reorder(t, order):
+    """The same [blk, head, tok, d] values in another storage order: tokens before
+    heads, rows with 16 more elements behind them, or blocks innermost of the three."""
+    if order == "tokens":
+        return t.transpose(1, 2).contiguous().transpose(1, 2)
+    if order == "padded":
+        wide = torch.empty(t.shape[:3] + (t.shape[3] + 16,), dtype=t.dtype, device=t.device)
+        wide[..., : t.shape[3]].copy_(t)
+        return wide[..., : t.shape[3]]
+    return t.permute(1, 2, 0, 3).contiguous().permute(2, 0, 1, 3)
+
+
+@pytest.mark.parametrize("order", ["tokens", "padded", "blocks"])
+@pytest.mark.parametrize("kv,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("fp8", 64)])
+def test_storage_orders(kv, D, order):
+    """Strides other than [blk, head, tok, d]: verify on contiguous and paged caches
+    and drafts, whole and on the partition, equal what the usual order gives, bit for
+    bit."""
+    banner(f"fp32 path: storage order {order} {kv} D={D}")
+
+    def store(t):
+        return _reorder(t.view(torch.uint8), order).view(t.dtype) if kv == "fp8" else _reorder(t, order)
+
+    for ps in (0, 16):
+        inp = W.make_verify_inputs(_spec(kv, D, 3, 4, B=5, ctx_lo=1, ctx_hi=400, page_size=ps), 91 + ps, device=DEV)
+        want = run_verify(inp)
+        inp.k_cache, inp.v_cache = store(inp.k_cache), store(inp.v_cache)
+        got = run_verify(inp)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    spec = W.DraftSpec(B=7, Hq=8, Hkv=2, D=D, S=4, W=100, steps=1, ctx_lo=1, ctx_hi=300, kv_dtype=kv,
+                       q_dtype="f32" if kv == "f32" else "bf16")
+    for kernel in (0, 2):
+        d = W.make_draft_inputs(spec, 95, device=DEV)
+        W.write_step_token(d, 0)
+        want = run_draft(d, 0, kernel=kernel)
+        d.sink_k, d.sink_v, d.ring_k, d.ring_v = store(d.sink_k), store(d.sink_v), store(d.ring_k), store(d.ring_v)
+        got = run_draft(d, 0, kernel=kernel)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
